@@ -56,6 +56,9 @@ constexpr int PREFILL_KPS = 1024; // keys per attention split in prefill chunks 
 constexpr int ATTN_KPS = 256;     // keys per attention split of a step pass, doubled while the grid is too
 constexpr int ATTN_GRID_CAP = 1280; // large (batch x KV heads x splits above this, 5 per CU) or there are
 constexpr int ATTN_SPLIT_CAP = 16;  // more splits than this (their partials cost the merge a load each)
+constexpr int LM_BIG_MT = 20;    // LM heads of more m-tiles stay on the large-M GEMM
+constexpr int ROWS_MIN_MT = 3;   // bf16 passes of more than 32 rows use the GEMM of pbd_gemm.hip, unless
+constexpr int ROWS_MIN_KB = 8;   // hidden < 256, where its eight K-splitting waves would have no K step each
 constexpr int BIG_MIN_MT = 8;    // passes of >= 128 rows (prefill chunks, batches of 8+) use the large-M projection
 constexpr size_t MAX_LDS = 160 * 1024;   // LDS one gfx950 work-group may allocate
 constexpr unsigned PBD_DEFAULT_WAIT = 1u << 18;   // polls per wait of the persistent pass (~0.25 s)
@@ -92,6 +95,7 @@ struct Layout {
     size_t w_kpart, w_kcnt;                          // split-K partial tiles and arrival counters
     size_t w_arg_mx, w_arg_sum;                      // LM-head softmax partials (draft confidence)
     size_t w_xc[2], w_sqc;                           // prefill: gathered last rows (LM-head operand, Σx² partials)
+    bool rows;                                       // passes of >= ROWS_MIN_MT m-tiles use launch_gemm_rows
     bool big;                                        // passes of >= BIG_MIN_MT m-tiles can use the large-M GEMM
     size_t w_u;                                      // its LoRA shrink u = A x, [M][sources * RT * 16] fp32
     size_t w_ukpart;                                 // the shrink's split-K slices [BIG_KSPLIT_MAX][w_u]
@@ -242,8 +246,11 @@ void make_layout(const pbd_config* c, Layout& y) {
     y.w_xc[0] = take(y.kb_e * xfc); y.w_xc[1] = take(nlo * y.kb_e * xfc);
     y.w_sqc = take((size_t)std::max(y.tiles_d, 1) * y.Bmax * 4);
     y.big = y.Mmax >= BIG_MIN_MT * 16;
-    y.w_u = y.big && y.r > 0 ? take((size_t)y.Mmax * 3 * y.RT * 16 * 4) : 0;   // LoRA shrink, large-M path
-    y.w_ukpart = y.w_u ? take((size_t)BIG_KSPLIT_MAX * y.Mmax * 3 * y.RT * 16 * 4) : 0;
+    // LoRA shrink of the projections of many rows
+    y.rows = y.dtype == PBD_DTYPE_BF16 && y.kb_gu >= ROWS_MIN_KB;
+    const bool any_u = y.r > 0 && (y.rows ? y.MTmax >= ROWS_MIN_MT : y.big);
+    y.w_u = any_u ? take((size_t)y.Mmax * 3 * y.RT * 16 * 4) : 0;
+    y.w_ukpart = y.w_u && !y.rows ? take((size_t)BIG_KSPLIT_MAX * y.Mmax * 3 * y.RT * 16 * 4) : 0;
     y.w_dn_conf = take((size_t)y.Bmax * y.D * 4);
     // (its byte offsets into the packed weights are 32-bit)
     y.fused_shape = fused_cand && y.packed_bytes < ((size_t)1 << 32);
@@ -380,6 +387,9 @@ int run_pass(pbd_ctx* c, const PassReq& q, hipStream_t st) {
     // large-M draft/verify passes of bf16 models: single fp16 activation
     // operands against the fp16 weight copies (one MFMA per fragment pair)
     const bool h16 = big && !pre && y.f16big;
+    // bf16 passes of more than two m-tiles (more than the skinny GEMM takes in
+    // one go over its weights)
+    const bool rows = y.rows && MT >= ROWS_MIN_MT;
     const bool split = c->split && dt == PBD_DTYPE_BF16 && !h16;
     float* x = (float*)(ws + y.w_x);
     float* sq_a = (float*)(ws + y.w_sq_a);
@@ -526,7 +536,7 @@ int run_pass(pbd_ctx* c, const PassReq& q, hipStream_t st) {
         ka.S = cdiv(g.kb, shrink_kper(g, nsrc));
         return launch_ksum(ka, st);
     };
-    auto launch_big = [&](const FGemmArgs& g, int nsrc, int epi = EPI_STORE) -> hipError_t {
+    auto epi_args = [&](const FGemmArgs& g, int nsrc, int epi) {
         BigGemmArgs b = big_args(g);
         if (epi == EPI_SWIGLU) { b.sw_hi = g.nx_hi; b.sw_lo = g.nx_lo; b.sw_MT = g.n_MT; }
         if (epi == EPI_RESID) {
@@ -538,8 +548,31 @@ int run_pass(pbd_ctx* c, const PassReq& q, hipStream_t st) {
             b.tile_split0 = g.tile_split0; b.tile_split1 = g.tile_split1;
             b.W = g.W; b.adapter_from = g.adapter_from; b.scale = g.scale; b.lb = g.lb;
         }
-        return launch_gemm_big(dt, b, st);
+        return b;
     };
+    auto launch_big = [&](const FGemmArgs& g, int nsrc, int epi) -> hipError_t {
+        return launch_gemm_big(dt, epi_args(g, nsrc, epi), st);
+    };
+    // launch_gemm_rows' LoRA: the shrink inside the projection, or one launch over
+    // the stacked A tiles into u before it
+    auto rows_shrink = [&](const FGemmArgs& g, int nsrc) -> hipError_t {
+        const size_t src_frags = (size_t)y.RT * g.kb * 64;
+        for (int i = 1; i < nsrc; ++i)
+            if (g.la[i] != g.la[0] + i * src_frags) return hipErrorInvalidValue;
+        BigGemmArgs sh{};
+        sh.w = g.la[0]; sh.n_tiles = nsrc * y.RT; sh.kb = g.kb; sh.xhi = g.xhi; sh.xlo = g.xlo;
+        sh.M = g.M; sh.MT = g.MT; sh.out = ubig; sh.ldo = nsrc * y.RT * 16; sh.op_f16 = h16 ? 1 : 0;
+        return launch_gemm_rows(sh, st);
+    };
+#define PBD_ROWS(G, NSRC, EPI, WHAT)                                                                       \
+    do {                                                                                                \
+        BigGemmArgs kb_ = epi_args(G, NSRC, EPI);                                                       \
+        if (lora) {                                                                                     \
+            if (gemm_rows_shrink_tiles(kb_) > 0) kb_.la = (G).la[0];                                      \
+            else PBD_TIMED(c, st, PBD_KCLASS_GEMM, rows_shrink(G, NSRC), WHAT " (LoRA shrink)");          \
+        }                                                                                               \
+        PBD_TIMED(c, st, PBD_KCLASS_GEMM, launch_gemm_rows(kb_, st), WHAT);                               \
+    } while (0)
 #define PBD_BIG(G, NSRC, EPI, WHAT)                                                                      \
     do {                                                                                                \
         if (lora) {                                                                                     \
@@ -560,7 +593,8 @@ int run_pass(pbd_ctx* c, const PassReq& q, hipStream_t st) {
         for (int i = 0; i < 3; ++i) g.la[i] = (const uint4*)(pk + (h16 ? lo_.la16[i] : lo_.la[i]));
         g.lb = pk + lo_.lb_qkv;
         g.out = (float*)(ws + y.w_qkv); g.ldo = y.nqkv;
-        if (big) PBD_BIG(g, 3, EPI_STORE, "qkv gemm");
+        if (rows) PBD_ROWS(g, 3, EPI_STORE, "qkv gemm");
+        else if (big) PBD_BIG(g, 3, EPI_STORE, "qkv gemm");
         else PBD_TIMED(c, st, PBD_KCLASS_GEMM, launch_fgemm(dt, g, EPI_STORE, st), "qkv gemm");
 
         AttnArgs at{};
@@ -629,7 +663,9 @@ int run_pass(pbd_ctx* c, const PassReq& q, hipStream_t st) {
         g.x = x; g.ldx = y.H; g.gnext = pk + lo_.mlp_norm; g.nx_hi = hi(y.w_xm); g.nx_lo = lo(y.w_xm); g.n_MT = MT;
         g.sq_out = sq_m;
         split_k(g);
-        if (big) {
+        if (rows) {
+            PBD_ROWS(g, 1, EPI_RESID, "o gemm");
+        } else if (big) {
             PBD_BIG(g, 1, EPI_RESID, "o gemm");
         } else {
             PBD_TIMED(c, st, PBD_KCLASS_GEMM, launch_fgemm(dt, g, EPI_RESID, st), "o gemm");
@@ -643,7 +679,9 @@ int run_pass(pbd_ctx* c, const PassReq& q, hipStream_t st) {
         g.la[1] = (const uint4*)(pk + (h16 ? lo_.la16[5] : lo_.la[5]));
         g.lb = pk + lo_.lb_gu;
         g.nx_hi = hi(y.w_xd); g.nx_lo = lo(y.w_xd); g.n_MT = MT;
-        if (big) {
+        if (rows) {
+            PBD_ROWS(g, 2, EPI_SWIGLU, "gate/up gemm");
+        } else if (big) {
             // SwiGLU in the GEMM epilogue: the down projection's operand directly
             PBD_BIG(g, 2, EPI_SWIGLU, "gate/up gemm");
         } else {
@@ -658,7 +696,9 @@ int run_pass(pbd_ctx* c, const PassReq& q, hipStream_t st) {
         g.gnext = l + 1 < L ? pk + y.lay[l + 1].attn_norm : pk + y.p_final_norm;
         g.nx_hi = hi(y.w_xa); g.nx_lo = lo(y.w_xa); g.n_MT = MT; g.sq_out = sq_a;
         split_k(g);
-        if (big) {
+        if (rows) {
+            PBD_ROWS(g, 1, EPI_RESID, "down gemm");
+        } else if (big) {
             PBD_BIG(g, 1, EPI_RESID, "down gemm");
         } else {
             PBD_TIMED(c, st, PBD_KCLASS_GEMM, launch_fgemm(dt, g, EPI_RESID, st), "down gemm");
@@ -693,6 +733,13 @@ int run_pass(pbd_ctx* c, const PassReq& q, hipStream_t st) {
     if (lmhead_fits(y.kb_e, lm_MT)) {
         n_part = std::min(y.tiles_e, LMHEAD_GRID);
         PBD_TIMED(c, st, PBD_KCLASS_LMHEAD, launch_lmhead(dt, ge, n_part, st), "lm head");
+    } else if (y.rows && lm_MT >= ROWS_MIN_MT && lm_MT < LM_BIG_MT) {
+        BigGemmArgs b = big_args(ge);
+        b.out = nullptr; b.logits = ge.logits; b.ldo = y.V;
+        b.arg_val = ge.arg_val; b.arg_idx = ge.arg_idx; b.arg_mx = ge.arg_mx; b.arg_sum = ge.arg_sum;
+        b.exclude = ge.exclude; b.excl_from = ge.excl_from; b.W = ge.W;
+        n_part = gemm_rows_parts(b);
+        PBD_TIMED(c, st, PBD_KCLASS_LMHEAD, launch_gemm_rows(b, st), "lm head");
     } else if (big && !pre) {
         // many rows: the large-M GEMM with the argmax epilogue, m-blocks
         // fastest so that the row blocks sharing an embedding tile run together
@@ -717,6 +764,7 @@ int run_pass(pbd_ctx* c, const PassReq& q, hipStream_t st) {
     return PBD_OK;
 }
 #undef PBD_BIG
+#undef PBD_ROWS
 
 int check_ctx(const pbd_ctx* c) {
     if (!c) { g_init_error = "context is NULL"; return PBD_ERR_INVALID_ARG; }

@@ -124,6 +124,77 @@ __device__ __host__ __forceinline__ size_t vblock_elem(int key, int dim) {
 // memory needs its own wait.
 __device__ __forceinline__ void lds_sync() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
+// 16 wait states, with nothing scheduled across: enough for any MFMA of this
+// file to finish writing its result, or reading its operands, before the
+// instructions that follow touch those registers
+__device__ __forceinline__ void mfma_settle() {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 7\n\ts_nop 7" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// acc += A(4 k per lane) * p, with p carried as bf16 value + bf16 residual
+__device__ __forceinline__ void mma_k4_split(f32x4& acc, const uint2& a, const f32x4& p) {
+    f32x4 h, l;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        h[e] = (float)(bf16)p[e];
+        l[e] = p[e] - h[e];
+    }
+    mma_k4(acc, a, h);
+    mma_k4(acc, a, l);
+}
+__device__ __forceinline__ void mma_k4_split(f32x4& acc, const uint4& a, const f32x4& p) { mma_k4(acc, a, p); }
+
+static __device__ __forceinline__ int ceil_div(int a, int b) { return (a + b - 1) / b; }
+
+// Split-KV schedule shared by the attention kernels and k_combine: prefix splits s < s_pre
+// cover keys [0, t) in chunks of `chunk` keys (a multiple of 16); split s_pre
+// holds the W block keys.  s_launch >= 2.
+static __device__ __forceinline__ void attn_splits(int t, int kps, int s_launch, int& s_pre, int& chunk) {
+    s_pre = t > 0 ? min(ceil_div(t, kps), s_launch - 1) : 0;
+    chunk = s_pre > 0 ? ceil_div(ceil_div(t, s_pre), 16) * 16 : 16;
+}
+
+// Write EPL consecutive k values of one operand row (16-byte aligned run of
+// one lane's fragment slot) as value and residual, or plain T when lo is null;
+// with h16 (bf16 models only) as fp16 values into hi.
+template <typename T>
+static __device__ __forceinline__ void put_operand_run(T* hi, T* lo, size_t e, const float* v, bool h16 = false) {
+    constexpr int EPL = Elt<T>::EPL;
+    if constexpr (EPL == 8) {
+        if (h16) {
+            _Float16 hh[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) hh[i] = (_Float16)v[i];
+            uint4 hv;
+            __builtin_memcpy(&hv, hh, 16);
+            *(uint4*)(hi + e) = hv;
+            return;
+        }
+    }
+    T h[EPL], l[EPL];
+#pragma unroll
+    for (int i = 0; i < EPL; ++i) {
+        h[i] = from_f32<T>(v[i]);
+        l[i] = from_f32<T>(v[i] - to_f32(h[i]));
+    }
+    uint4 hv, lv;
+    __builtin_memcpy(&hv, h, 16);
+    __builtin_memcpy(&lv, l, 16);
+    *(uint4*)(hi + e) = hv;
+    if (lo) *(uint4*)(lo + e) = lv;
+}
+
+// Write v into an operand as bf16 value (hi) plus bf16 residual (lo), or as
+// plain T when lo is null.
+template <typename T>
+static __device__ __forceinline__ void put_operand(T* hi, T* lo, size_t e, float v) {
+    const T h = from_f32<T>(v);
+    hi[e] = h;
+    if (lo) lo[e] = from_f32<T>(v - to_f32(h));
+}
+
 // ---------------------------------------------------------------------------
 // Wave reductions
 // ---------------------------------------------------------------------------

@@ -219,6 +219,10 @@ struct BigGemmArgs {
     // w points to fp16 copies of the weight fragments, and the residual /
     // SwiGLU epilogues write fp16 operands (rn_lo / sw_lo unused)
     int op_f16;
+    // pbd_gemm.hip: block grid, set by its launchers; the LoRA A tiles
+    // [sources * lrt][kb] whose shrink runs inside the launch (null: from u)
+    int gm, gn, xmap;
+    const void* la;
 };
 
 struct CombineArgs {
@@ -323,6 +327,13 @@ struct KSumArgs {
 };
 hipError_t launch_ksum(const KSumArgs& a, hipStream_t st);
 hipError_t launch_gemm_big(int dtype, const BigGemmArgs& a, hipStream_t st);   // split iff a.xlo
+// Passes of more than two m-tiles of bf16 models (pbd_gemm.hip).  With the
+// adapter (a.lrt > 0): gemm_rows_shrink_tiles > 0 says that the launch runs the
+// shrink itself, on a.la; else a.u holds it.  The argmax epilogue leaves
+// gemm_rows_parts partials per row.
+hipError_t launch_gemm_rows(const BigGemmArgs& a, hipStream_t st);
+int gemm_rows_shrink_tiles(const BigGemmArgs& a);
+int gemm_rows_parts(const BigGemmArgs& a);
 hipError_t launch_remask(const RemaskArgs& a, int batch, hipStream_t st);
 hipError_t launch_pack(int dtype, const PackArgs& a, hipStream_t st);
 hipError_t launch_pack_expand(int dtype, const PackExpandArgs& a, hipStream_t st);
