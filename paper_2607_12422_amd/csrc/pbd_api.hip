@@ -374,10 +374,12 @@ int run_pass(pbd_ctx* c, const PassReq& q, hipStream_t st) {
     }
     if (pre) kps = std::max(kps, PREFILL_KPS);
     const int s_launch = pre ? y.S_pre : std::min(y.S_max, cdiv(y.max_seq, kps) + 1);   // split-KV grid columns
+    // draft and verify passes of bf16 models take launch_attn_rows; other shapes
     // one work-group per 16 query rows: always for prefill chunks; by default
     // when the split grid leaves CUs idle or a work item has at most three
     // query tiles (the one-tile work-group runs two waves per SIMD)
-    const bool qsplit = pre || c->qsplit > 0 || (c->qsplit < 0 && (QT <= 3 || B * y.NKV * s_launch < 256));
+    const bool att_rows = c->qsplit <= 0 && attn_rows_fits(dt, y.HD, QT, pre ? 1 : 0, W);
+    const bool qsplit = !att_rows && (pre || c->qsplit > 0 || (c->qsplit < 0 && (QT <= 3 || B * y.NKV * s_launch < 256)));
     const int QTw = qsplit ? 1 : QT;                // ... per attention work-group
     const float scale = y.r > 0 ? c->cfg.lora_alpha / (float)y.r : 0.f;
     const bool lora = q.adapter && y.r > 0;
@@ -618,7 +620,7 @@ int run_pass(pbd_ctx* c, const PassReq& q, hipStream_t st) {
             const int slots = B * y.NKV * at.n_qgrp;
             const int free_wg = 256 - s_launch * slots;
             at.pf_x = slots > 0 && free_wg > slots ? free_wg / slots : 0;
-            size_t cap = (size_t)at.pf_x * slots * 256 * 16 * 128;
+            size_t cap = (size_t)at.pf_x * slots * (att_rows ? (QT + 1) * 64 : 256) * 16 * 128;
             at.pf[0] = pk + beg;
             at.pf_bytes[0] = std::min(end - beg, cap);
             cap -= at.pf_bytes[0];
@@ -639,16 +641,8 @@ int run_pass(pbd_ctx* c, const PassReq& q, hipStream_t st) {
             kw.kcache = at.kcache; kw.vcache = at.vcache;
             PBD_TIMED(c, st, PBD_KCLASS_OTHER, launch_kvwrite(dt, y.HD, kw, B, st), "prefill K/V");
         }
-        // four or five query tiles per KV head: one wave per query tile (keys
-        // staged in LDS); k_attn then only warms the cache, when CUs are spare
-        if (!pre && QTw == QT && attn_rows_fits(dt, y.HD, QTw, at.chunk, W)) {
-            at.skip_prefix = 1;
-            PBD_TIMED(c, st, PBD_KCLASS_ATTN, launch_attn_rows(at, QTw, B, st), "attention");
-            if (at.pf_x > 0)
-                PBD_TIMED(c, st, PBD_KCLASS_OTHER, launch_attn(dt, y.HD, QTw, at, B, st), "attention cache warming");
-        } else {
-            PBD_TIMED(c, st, PBD_KCLASS_ATTN, launch_attn(dt, y.HD, QTw, at, B, st), "attention");
-        }
+        if (att_rows) PBD_TIMED(c, st, PBD_KCLASS_ATTN, launch_attn_rows(at, QT, B, st), "attention");
+        else PBD_TIMED(c, st, PBD_KCLASS_ATTN, launch_attn(dt, y.HD, QTw, at, B, st), "attention");
 
         CombineArgs cb{};
         cb.W = W; cb.n_q = y.NQ; cb.head_dim = y.HD; cb.kps = kps; cb.s_launch = s_launch; cb.MT = MT;

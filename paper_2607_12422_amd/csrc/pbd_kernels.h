@@ -119,9 +119,6 @@ struct AttnArgs {
     // positions t..t+nrows-1; every key is read from the cache, causal inside
     // the chunk; no block split and no K/V writes
     int chunk;
-    // every split is run by k_attn_rows (launch_attn_rows); k_attn only warms
-    // the memory-side cache in its pf_x extra columns
-    int skip_prefix;
 };
 
 // Prefill chunk K/V: norm + RoPE of the W rows' keys, appended with the values.
