@@ -379,6 +379,7 @@ int run_pass(pbd_ctx* c, const PassReq& q, hipStream_t st) {
     // when the split grid leaves CUs idle or a work item has at most three
     // query tiles (the one-tile work-group runs two waves per SIMD)
     const bool att_rows = c->qsplit <= 0 && attn_rows_fits(dt, y.HD, QT, pre ? 1 : 0, W);
+    const bool att_chunk = pre && attn_chunk_fits(dt, y.HD);
     const bool qsplit = !att_rows && (pre || c->qsplit > 0 || (c->qsplit < 0 && (QT <= 3 || B * y.NKV * s_launch < 256)));
     const int QTw = qsplit ? 1 : QT;                // ... per attention work-group
     const float scale = y.r > 0 ? c->cfg.lora_alpha / (float)y.r : 0.f;
@@ -612,6 +613,7 @@ int run_pass(pbd_ctx* c, const PassReq& q, hipStream_t st) {
         at.q_norm = pk + lo_.q_norm; at.k_norm = pk + lo_.k_norm; at.rope = (const float2*)(pk + y.p_rope);
         at.kcache = c->kv; at.vcache = c->kv + y.kv_half;
         at.part_o = (float*)(ws + y.w_attn_o); at.part_ml = (float*)(ws + y.w_attn_ml);
+        at.MT = MT; at.op_hi = hi(y.w_xo); at.op_lo = lo(y.w_xo);
         // spare CUs during the attention warm the O, gate/up and down weights of
         // this layer and the q/k/v weights of the next one, then the next
         // layer's K/V of the batch's sequences when that slab is small
@@ -642,13 +644,16 @@ int run_pass(pbd_ctx* c, const PassReq& q, hipStream_t st) {
             PBD_TIMED(c, st, PBD_KCLASS_OTHER, launch_kvwrite(dt, y.HD, kw, B, st), "prefill K/V");
         }
         if (att_rows) PBD_TIMED(c, st, PBD_KCLASS_ATTN, launch_attn_rows(at, QT, B, st), "attention");
+        else if (att_chunk) PBD_TIMED(c, st, PBD_KCLASS_ATTN, launch_attn_chunk(at, B, st), "attention");
         else PBD_TIMED(c, st, PBD_KCLASS_ATTN, launch_attn(dt, y.HD, QTw, at, B, st), "attention");
 
-        CombineArgs cb{};
-        cb.W = W; cb.n_q = y.NQ; cb.head_dim = y.HD; cb.kps = kps; cb.s_launch = s_launch; cb.MT = MT;
-        cb.pos0 = pos0; cb.part_o = at.part_o; cb.part_ml = at.part_ml;
-        cb.op_hi = hi(y.w_xo); cb.op_lo = lo(y.w_xo); cb.op_f16 = h16 ? 1 : 0;
-        PBD_TIMED(c, st, PBD_KCLASS_COMBINE, launch_combine(dt, cb, M, st), "attention combine");
+        if (!att_chunk) {
+            CombineArgs cb{};
+            cb.W = W; cb.n_q = y.NQ; cb.head_dim = y.HD; cb.kps = kps; cb.s_launch = s_launch; cb.MT = MT;
+            cb.pos0 = pos0; cb.part_o = at.part_o; cb.part_ml = at.part_ml;
+            cb.op_hi = hi(y.w_xo); cb.op_lo = lo(y.w_xo); cb.op_f16 = h16 ? 1 : 0;
+            PBD_TIMED(c, st, PBD_KCLASS_COMBINE, launch_combine(dt, cb, M, st), "attention combine");
+        }
 
         // O projection + residual; writes the MLP RMSNorm operand
         base_gemm(g, h16 ? lo_.o16 : lo_.o, y.tiles_o, y.kb_o, y.w_xo);

@@ -12,8 +12,7 @@ namespace pbd {
 // exceeds it by more than this (log2 units)
 constexpr float RESCALE_SLACK = 8.f;
 
-// One stage of the ring: two 16-key blocks of the cache, each 4 KiB of K then
-// 4 KiB of V
+// 32 keys in LDS: two 16-key blocks of the cache, each 4 KiB of K then 4 KiB of V
 constexpr int ATTN_STAGE = 16384;
 
 // Work-groups past the splits warm the memory-side cache with what the next
@@ -41,20 +40,21 @@ static __device__ __forceinline__ void attn_warm(const AttnArgs& a) {
     asm volatile("" ::"v"(acc));
 }
 
-// The loader wave: stages 0 .. n_st - 1 of key blocks kb0, kb0 + 1, .. (no
-// block past kb_last is read: it is repeated, its keys are masked) into the
-// ring, RING - 1 stages ahead.  kc, vc: the head's cache plus 16 bytes per
-// lane.  Takes part in one barrier per stage, which opens that stage.
-template <int RING>
+// The loader wave: stages 0 .. n_st - 1 of NB key blocks each, from block kb0
+// on (no block past kb_last is read: it is repeated, its keys are masked), into
+// the ring, RING - 1 stages ahead.  kc, vc: the head's cache plus 16 bytes per
+// lane.  `before` runs once the first loads are on their way.  Takes part in
+// one barrier per stage, which opens that stage.
+template <int RING, int NB, typename BEFORE>
 static __device__ __forceinline__ void attn_loader(const char* kc, const char* vc, int kb0, int kb_last, int n_st,
-                                                   unsigned char* ring) {
+                                                   unsigned char* ring, BEFORE before) {
     typedef __attribute__((address_space(3))) void* lds;
-    static_assert(RING >= 3 && RING <= 5 && 16 * (RING - 2) < 64, "loads in flight fit the wait counter");
+    static_assert(RING >= 2 && RING <= 5 && 8 * NB * (RING - 2) < 64, "loads in flight fit the wait counter");
     auto issue = [&](int st, int slot) {
-        unsigned char* dst = ring + (size_t)slot * ATTN_STAGE;
+        unsigned char* dst = ring + (size_t)slot * NB * 8192;
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            const size_t off = (size_t)min(kb0 + 2 * st + c, kb_last) * 4096;
+        for (int c = 0; c < NB; ++c) {
+            const size_t off = (size_t)min(kb0 + NB * st + c, kb_last) * 4096;
 #pragma unroll
             for (int i = 0; i < 4; ++i)
                 __builtin_amdgcn_global_load_lds((const void*)(kc + off + i * 1024), (lds)(dst + c * 8192 + i * 1024),
@@ -68,13 +68,14 @@ static __device__ __forceinline__ void attn_loader(const char* kc, const char* v
 #pragma unroll
     for (int s = 0; s < RING - 1; ++s)
         if (s < n_st) issue(s, s);
+    before();
     int slot = RING - 1;
     for (int it = 0; it < n_st; ++it) {
-        // 16 loads a stage; those of the stages after `it` may stay in flight
+        // 8 NB loads a stage; those of the stages after `it` may stay in flight
         const int left = min(n_st - 1 - it, RING - 2);
-        if (left >= 3) asm volatile("s_waitcnt vmcnt(48)\n\ts_barrier" ::: "memory");
-        else if (left == 2) asm volatile("s_waitcnt vmcnt(32)\n\ts_barrier" ::: "memory");
-        else if (left == 1) asm volatile("s_waitcnt vmcnt(16)\n\ts_barrier" ::: "memory");
+        if (left >= 3) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(RING >= 5 ? 24 * NB : 0) : "memory");
+        else if (left == 2) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(RING >= 4 ? 16 * NB : 0) : "memory");
+        else if (left == 1) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(RING >= 3 ? 8 * NB : 0) : "memory");
         else asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
         // the stage read last turn (before this barrier) gives its slot
         if (it + RING - 1 < n_st) issue(it + RING - 1, slot);

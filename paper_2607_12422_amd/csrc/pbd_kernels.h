@@ -119,6 +119,11 @@ struct AttnArgs {
     // positions t..t+nrows-1; every key is read from the cache, causal inside
     // the chunk; no block split and no K/V writes
     int chunk;
+    // launch_attn_chunk writes the O-projection operand itself: fragments
+    // [n_q head_dim / 32][MT], value and residual
+    int MT;
+    void* op_hi;
+    void* op_lo;
 };
 
 // Prefill chunk K/V: norm + RoPE of the W rows' keys, appended with the values.
@@ -304,6 +309,10 @@ int fgemm_threads(int epi);         // work-group size of the GEMM with epilogue
 // (false: this shape is not covered; use k_attn alone)
 bool attn_rows_fits(int dtype, int head_dim, int qt, int chunk, int W);
 hipError_t launch_attn_rows(const AttnArgs& a, int qt, int batch, hipStream_t st);
+// Prefill chunks (bf16, head_dim 128): every key of a 64-query-row block in one
+// work-group, O operand written directly (no partials, no merge)
+bool attn_chunk_fits(int dtype, int head_dim);
+hipError_t launch_attn_chunk(const AttnArgs& a, int batch, hipStream_t st);
 hipError_t launch_attn(int dtype, int head_dim, int qt, const AttnArgs& a, int batch, hipStream_t st);
 hipError_t launch_combine(int dtype, const CombineArgs& a, int M, hipStream_t st);
 hipError_t launch_argmax(const ArgmaxArgs& a, hipStream_t st);

@@ -1069,7 +1069,7 @@ __global__ __launch_bounds__((QT + 1) * 64) __attribute__((amdgpu_waves_per_eu(3
     if (wid == QT && !blk) {
         const char* kc = (const char*)((const T*)a.kcache + head) + lane * 16;
         const char* vc = (const char*)((const T*)a.vcache + head) + lane * 16;
-        attn_loader<RING>(kc, vc, k_lo / 16, ceil_div(k_hi, 16) - 1, n_st, smem);
+        attn_loader<RING, 2>(kc, vc, k_lo / 16, ceil_div(k_hi, 16) - 1, n_st, smem, [] {});
         return;
     }
 

@@ -51,3 +51,28 @@ def test_tiles_and_splits_match_oracle(block, lengths, kps):
         ok = decisive(ref_vl, 2e-2)
         assert np.array_equal(v[b].cpu().numpy()[ok], ref_p[ok])
     g.close()
+
+
+@pytest.mark.parametrize("chunk,lengths", [
+    (1, [3, 5, 1]),                 # one row per pass
+    (31, [40, 1, 62]),              # a row block over both query heads
+    (64, [64, 65, 129]),            # one block per head; a sequence of one chunk
+    (100, [350, 7, 100]),           # a short sequence ends before the last chunks
+    (300, [700, 301, 5]),           # several stages, causal rows in the last ones
+    (513, [513, 512, 130]),         # a last block with two rows
+])
+def test_prefill_chunks_match_oracle(chunk, lengths):
+    cfg = SHAPE
+    w = synth.make_weights(cfg, 92)
+    prompts = synth.make_prompts(cfg, lengths, 9)
+    g = GpuRun(cfg, w, max_batch=3, max_seq=max(lengths) + 2 * cfg.width, prefill_chunk=chunk)
+    first = g.prefill(prompts)
+    v, vlg = g.verify(g.i32(np.full((3, cfg.block), 9)))
+    assert g.status() == 0
+    m = om.OracleModel(w)
+    for b in range(3):
+        st = om.prefill(m, prompts[b])
+        st.anchor = int(first[b])
+        _, ref, _, _ = om.verify(m, st, np.full(cfg.block, 9))
+        assert np.abs(vlg[b].cpu().numpy() - ref).max() <= 2e-2
+    g.close()
