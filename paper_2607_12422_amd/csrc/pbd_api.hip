@@ -56,7 +56,6 @@ constexpr int PREFILL_KPS = 1024; // keys per attention split in prefill chunks 
 constexpr int ATTN_KPS = 256;     // keys per attention split of a step pass, doubled while the grid is too
 constexpr int ATTN_GRID_CAP = 1280; // large (batch x KV heads x splits above this, 5 per CU) or there are
 constexpr int ATTN_SPLIT_CAP = 16;  // more splits than this (their partials cost the merge a load each)
-constexpr int LM_BIG_MT = 20;    // LM heads of more m-tiles stay on the large-M GEMM
 constexpr int ROWS_MIN_MT = 3;   // bf16 passes of more than 32 rows use the GEMM of pbd_gemm.hip, unless
 constexpr int ROWS_MIN_KB = 8;   // hidden < 256, where its eight K-splitting waves would have no K step each
 constexpr int BIG_MIN_MT = 8;    // passes of >= 128 rows (prefill chunks, batches of 8+) use the large-M projection
@@ -732,7 +731,7 @@ int run_pass(pbd_ctx* c, const PassReq& q, hipStream_t st) {
     if (lmhead_fits(y.kb_e, lm_MT)) {
         n_part = std::min(y.tiles_e, LMHEAD_GRID);
         PBD_TIMED(c, st, PBD_KCLASS_LMHEAD, launch_lmhead(dt, ge, n_part, st), "lm head");
-    } else if (y.rows && lm_MT >= ROWS_MIN_MT && lm_MT < LM_BIG_MT) {
+    } else if (y.rows && lm_MT >= ROWS_MIN_MT) {
         BigGemmArgs b = big_args(ge);
         b.out = nullptr; b.logits = ge.logits; b.ldo = y.V;
         b.arg_val = ge.arg_val; b.arg_idx = ge.arg_idx; b.arg_mx = ge.arg_mx; b.arg_sum = ge.arg_sum;

@@ -18,88 +18,13 @@
 // 6.3, 9.3 and 7.8 us at 136 rows (64 x 64 blocks: 10.9, 13.6, 11.6, 19.3) and
 // 7.7, 6.6, 9.8 and 8.4 us at 68 rows of value + residual operands (12.3, 17.2,
 // 12.7, 24.3; the skinny GEMM 10.9, 18.8, 18.1, 18.8 in the pass).
-#include "pbd_device.h"
-#include "pbd_kernels.h"
+#include "pbd_epi.h"
 #include "pbd_launch.h"
 
 #include <algorithm>
 
 namespace pbd {
 namespace {
-
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-
-enum { KS_XN = 0, KS_XW = 1, KS_XM = 2 };
-
-// Work-group id -> (m-block, n-block); false: none.  Work-groups of one XCD
-// (id % 8; its own L2) take every eighth n-block.  Their share of the weights
-// stays in that L2 while the m-blocks go by (XN); weights too large for that
-// go by once, every m-block of an n-block following on (XW).  With few
-// n-blocks the XCDs share out the m-blocks (XM).
-__device__ __forceinline__ bool block_of(const BigGemmArgs& a, int& bm, int& bn) {
-    const int xcd = blockIdx.x % 8, id = blockIdx.x / 8, gn8 = (a.gn + 7) / 8;
-    bm = a.xmap == KS_XM ? (id / a.gn) * 8 + xcd : a.xmap == KS_XN ? id / gn8 : id % a.gm;
-    bn = a.xmap == KS_XM ? id % a.gn : (a.xmap == KS_XN ? id % gn8 : id / a.gm) * 8 + xcd;
-    return bm < a.gm && bn < a.gn;
-}
-
-__device__ __forceinline__ int lora_src(const BigGemmArgs& a, int nt) {
-    return a.lora_mode == LORA_BY_TILE ? (nt < a.tile_split0 ? 0 : nt < a.tile_split1 ? 1 : 2) : 0;
-}
-
-// What a tile's residual epilogue reads, requested ahead of it.
-struct Resid {
-    float4 x;
-    uint2 g;
-    __device__ __forceinline__ void load(const BigGemmArgs& a, int m, int nt, bool live, int lgrp) {
-        x = float4{0.f, 0.f, 0.f, 0.f};
-        g = uint2{0u, 0u};
-        if (a.rx && live) {
-            x = *(const float4*)(a.rx + (size_t)m * a.ldx + nt * 16 + lgrp * 4);
-            g = *(const uint2*)((const bf16*)a.rgain + nt * 16 + lgrp * 4);
-        }
-    }
-};
-
-// One tile's store (v scaled by r_m; lane: row lrow = m % 16, columns 4 lgrp
-// .. 4 lgrp + 3): q/k/v, the residual x += y with the next operand and the
-// row's sum of squares, or SwiGLU.  Every lane of the wave takes part.
-template <bool PAIR>
-__device__ __forceinline__ void put_tile(const BigGemmArgs& a, const f32x4& v, int m, int nt, bool live, int lgrp,
-                                         const Resid& r) {
-    const int col0 = nt * 16 + lgrp * 4;
-    if (a.rx) {
-        const float4 xo = r.x;
-        float xv4[4] = {xo.x + v[0], xo.y + v[1], xo.z + v[2], xo.w + v[3]};
-        if (!live) xv4[0] = xv4[1] = xv4[2] = xv4[3] = 0.f;
-        if (live) *(float4*)(a.rx + (size_t)m * a.ldx + col0) = float4{xv4[0], xv4[1], xv4[2], xv4[3]};
-        float ss = xv4[0] * xv4[0] + xv4[1] * xv4[1] + xv4[2] * xv4[2] + xv4[3] * xv4[3];
-        ss += __shfl_xor(ss, 16);
-        ss += __shfl_xor(ss, 32);
-        const bf16x4 g = __builtin_bit_cast(bf16x4, r.g);
-        float ov[8];                     // runs of eight values, four from the neighbouring lane group
-#pragma unroll
-        for (int e = 0; e < 4; ++e) ov[e] = xv4[e] * (float)g[e];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) ov[4 + e] = __shfl_xor(ov[e], 16);
-        if (live && (lgrp % 2) == 0)
-            put_operand_run<bf16>((bf16*)a.rn_hi, (bf16*)a.rn_lo, xfrag_elem<bf16>(m, col0, a.rn_MT), ov, !PAIR);
-        if (live && lgrp == 0) a.rsq[(size_t)nt * a.rsq_stride + m] = ss;
-    } else if (a.sw_hi) {
-        float h[8];                      // the lane's up values sit 32 lanes away (column + 8)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const float gt = v[e], up = __shfl_xor(v[e], 32);
-            h[e] = gt / (1.f + __expf(-gt)) * up;
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) h[4 + e] = __shfl_xor(h[e], 16);
-        if (live && lgrp == 0)
-            put_operand_run<bf16>((bf16*)a.sw_hi, (bf16*)a.sw_lo, xfrag_elem<bf16>(m, nt * 8, a.sw_MT), h, !PAIR);
-    } else if (live) {
-        *(float4*)(a.out + (size_t)m * a.ldo + col0) = float4{v[0], v[1], v[2], v[3]};
-    }
-}
 
 // One tile of the LM head: logits, and per row (into am / ai, lanes of group
 // 0) the best value and its column, and with confidence the maximum and the
@@ -392,18 +317,12 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 8)))
     }
 }
 
-int xcd_map(const BigGemmArgs& a) {
-    if (a.gn < 8 || (a.gn % 8 != 0 && a.gn < 64)) return KS_XM;
-    return (size_t)a.n_tiles * a.kb * 1024 / 8 <= ((size_t)2 << 20) ? KS_XN : KS_XW;
-}
-
 template <bool PAIR, int MB, int NB, int NW, int ST>
 hipError_t launch_ks(BigGemmArgs a, hipStream_t st) {
     a.gm = (a.MT + MB - 1) / MB;
     a.gn = (a.n_tiles + NB - 1) / NB;
     a.xmap = xcd_map(a);
-    const unsigned grid = a.xmap == KS_XM ? 8u * ((a.gm + 7) / 8) * a.gn : 8u * ((a.gn + 7) / 8) * a.gm;
-    PBD_LAUNCH((k_gemm_ks<PAIR, MB, NB, NW, ST>), dim3(grid), dim3(NW * 64), 0, st, a);
+    PBD_LAUNCH((k_gemm_ks<PAIR, MB, NB, NW, ST>), dim3(xcd_grid(a)), dim3(NW * 64), 0, st, a);
     return hipGetLastError();
 }
 
@@ -426,30 +345,60 @@ const Inst INST[] = {
 #undef KS
 #undef KS_LORA
 
-// Time (us, beyond a fixed 4) behind the choice of an instance, fitted to all
-// of them at 34 to 1056 rows: a CU takes in 70 KiB of fragments a
-// microsecond (the path from the L2 bounds the loop, not the MFMAs), 62 when
-// two work-groups of four waves share it, 45 when one of those runs alone;
-// eight waves fill a CU, so a second round starts after the first one's
-// epilogue.
-float gemm_cost(const Inst& c, int n_tiles, int kb, int MT) {
+// Times (us) behind the choice of an instance, fitted to all of them at 34 to
+// 4096 rows of the Qwen3-0.6B projections.
+//
+// K-split blocks: a CU takes in 70 KiB of fragments a microsecond (the path
+// from the L2 bounds the loop, not the MFMAs), 62 over rounds of two
+// work-groups of four waves; one of those alone has its start and end to
+// itself.  Eight waves fill a CU, so a second round starts after the first
+// one's epilogue.
+float ks_cost(const Inst& c, int n_tiles, int kb, int MT) {
     const long blocks = (long)((MT + c.mb - 1) / c.mb) * ((n_tiles + c.nb - 1) / c.nb);
     const float rounds = (float)((blocks + 255) / 256);
     const float kib = (float)kb * (c.nb + c.mb * (c.pair ? 2 : 1) + c.st);
-    if (c.nw == 8) return rounds * kib / 70.f + (rounds - 1.f) * 1.5f;
-    return blocks <= 256 ? kib / 45.f : rounds * kib / 62.f;
+    if (c.nw == 8) return 4.f + rounds * kib / 70.f + (rounds - 1.f) * 1.5f;
+    return blocks <= 256 ? 7.5f + kib / (c.pair ? 55.f : 80.f) : 4.f + rounds * kib / 62.f;
 }
 
-// The LM head's blocks (four waves, four tiles) leave one argmax partial per row.
-const Inst* gemm_pick(int pair, int st, int n_tiles, int kb, int MT, bool argmax) {
-    const Inst* best = nullptr;
-    float bc = 0.f;
-    for (const Inst& c : INST) {
-        if (c.pair != pair || c.st != st) continue;
-        if (argmax && (c.nw != 4 || c.nb != 4)) continue;
-        const float t = gemm_cost(c, n_tiles, kb, MT);
-        if (!best || t < bc) { best = &c; bc = t; }
-    }
+// LDS blocks: the same path (66 KiB a microsecond, 58 with operands in pairs,
+// whose twice as many products cover less of it), and an epilogue that grows
+// with the tiles of a wave and waits for the residual where there is one; one
+// work-group a CU.  At 1056 fp16 rows gate/up take 21.9 us in 8 x 16 tiles
+// (K-split: 28.6), q/k/v 16.8 in 10 x 8 (23.0), the LM head 414 in 12 x 12 or
+// 10 x 16 (64 x 64 and 128 x 128 blocks staged through registers: 768); at 1024
+// rows in pairs gate/up 27.5 in 8 x 12 (37.9) and q/k/v 18.8 in 8 x 8 (25.6).
+// With a quarter of the work-groups that the chip holds (o at 512 rows: 21.4
+// against 10.4) the K split stays.
+float tile_cost(const TileInst& c, int n_tiles, int kb, int MT, bool resid) {
+    const long blocks = (long)((MT + c.bm - 1) / c.bm) * ((n_tiles + c.bn - 1) / c.bn);
+    const float rounds = (float)((blocks + 255) / 256);
+    const float kib = (float)kb * (c.bn + c.bm * (c.pair ? 2 : 1));
+    const float epi = (c.pair ? 0.4f : 0.25f) * c.wtiles + (resid ? 4.f : 1.5f);
+    return 2.f + rounds * (kib / (c.pair ? 58.f : 66.f) + epi);
+}
+
+struct Pick {
+    hipError_t (*launch)(BigGemmArgs, hipStream_t);
+    int bn;
+    float us;
+};
+
+// The LM head's K-split blocks (four waves, four tiles) and the LDS blocks
+// made for it leave one argmax partial per row and block.
+Pick gemm_pick(int pair, int st, int n_tiles, int kb, int MT, bool argmax, bool resid) {
+    Pick best{nullptr, 0, 0.f};
+    auto take = [&](hipError_t (*launch)(BigGemmArgs, hipStream_t), int bn, float us) {
+        if (!best.launch || us < best.us) best = Pick{launch, bn, us};
+    };
+    for (const Inst& c : INST)
+        if (c.pair == pair && c.st == st && (!argmax || (c.nw == 4 && c.nb == 4)))
+            take(c.launch, c.nb, ks_cost(c, n_tiles, kb, MT));
+    int n = 0;
+    const TileInst* ti = tile_insts(&n);
+    for (int i = 0; i < n && st == 0 && kb % 2 == 0; ++i)
+        if (ti[i].pair == pair && ti[i].arg == (argmax ? 1 : 0))
+            take(ti[i].launch, ti[i].bn, tile_cost(ti[i], n_tiles, kb, MT, resid));
     return best;
 }
 
@@ -461,14 +410,14 @@ int gemm_rows_shrink_tiles(const BigGemmArgs& a) {
     const int st = (a.lora_mode == LORA_ROW_HALF ? 2 : 1) * a.lrt;
     if (a.lrt <= 0 || !(st == 1 || st == 2 || st == 4)) return 0;
     const int pair = a.op_f16 ? 0 : 1;
-    const float in = gemm_cost(*gemm_pick(pair, st, a.n_tiles, a.kb, a.MT, false), a.n_tiles, a.kb, a.MT);
-    const float ext = gemm_cost(*gemm_pick(pair, 0, a.n_tiles, a.kb, a.MT, false), a.n_tiles, a.kb, a.MT) + 4.5f;
+    const float in = gemm_pick(pair, st, a.n_tiles, a.kb, a.MT, false, a.rx != nullptr).us;
+    const float ext = gemm_pick(pair, 0, a.n_tiles, a.kb, a.MT, false, a.rx != nullptr).us + 4.5f;
     return in <= ext ? st : 0;
 }
 
 int gemm_rows_parts(const BigGemmArgs& a) {
-    const Inst* c = gemm_pick(a.op_f16 ? 0 : 1, 0, a.n_tiles, a.kb, a.MT, true);
-    return (a.n_tiles + c->nb - 1) / c->nb;
+    const Pick c = gemm_pick(a.op_f16 ? 0 : 1, 0, a.n_tiles, a.kb, a.MT, true, false);
+    return (a.n_tiles + c.bn - 1) / c.bn;
 }
 
 hipError_t launch_gemm_rows(const BigGemmArgs& a, hipStream_t st) {
@@ -483,8 +432,8 @@ hipError_t launch_gemm_rows(const BigGemmArgs& a, hipStream_t st) {
         // a block's tiles share their LoRA source (blocks of 1, 2 or 4 tiles)
         if (sh && a.lora_mode == LORA_BY_TILE && (a.tile_split0 % 4 || a.tile_split1 % 4)) return hipErrorInvalidValue;
     }
-    const Inst* c = gemm_pick(a.op_f16 ? 0 : 1, sh, a.n_tiles, a.kb, a.MT, a.arg_val != nullptr);
-    return c ? c->launch(a, st) : hipErrorInvalidValue;
+    const Pick c = gemm_pick(a.op_f16 ? 0 : 1, sh, a.n_tiles, a.kb, a.MT, a.arg_val != nullptr, a.rx != nullptr);
+    return c.launch ? c.launch(a, st) : hipErrorInvalidValue;
 }
 
 }  // namespace pbd
