@@ -56,8 +56,16 @@ constexpr int PREFILL_KPS = 1024; // keys per attention split in prefill chunks 
 constexpr int ATTN_KPS = 256;     // keys per attention split of a step pass, doubled while the grid is too
 constexpr int ATTN_GRID_CAP = 1280; // large (batch x KV heads x splits above this, 5 per CU) or there are
 constexpr int ATTN_SPLIT_CAP = 16;  // more splits than this (their partials cost the merge a load each)
-constexpr int ROWS_MIN_MT = 3;   // bf16 passes of more than 32 rows use the GEMM of pbd_gemm.hip, unless
-constexpr int ROWS_MIN_KB = 8;   // hidden < 256, where its eight K-splitting waves would have no K step each
+// bf16 models use the GEMM of pbd_gemm.hip unless hidden < 256, where its eight
+// K-splitting waves would have no K step each.  Few rows with an adapter of a
+// high rank stay on the skinny GEMM, whose shrink of any rank runs inside the
+// projection: more rank tiles than m-tiles, at most two m-tiles (draft over 14
+// layers, one 8-row block at rank 32: 662 us against 675; two at rank 64: 717
+// against 770).  Everything else is faster there (16 greedy rows: 1345 us a step
+// against 1438; two 16-row blocks at rank 16: 734 against 816, at rank 32: 716
+// against 757).
+constexpr int ROWS_MIN_KB = 8;
+constexpr int ROWS_MIN_MT = 3;   // m-tiles from which every rank does
 constexpr int BIG_MIN_MT = 8;    // passes of >= 128 rows (prefill chunks, batches of 8+) use the large-M projection
 constexpr size_t MAX_LDS = 160 * 1024;   // LDS one gfx950 work-group may allocate
 constexpr unsigned PBD_DEFAULT_WAIT = 1u << 18;   // polls per wait of the persistent pass (~0.25 s)
@@ -248,8 +256,10 @@ void make_layout(const pbd_config* c, Layout& y) {
     // LoRA shrink of the projections of many rows
     y.rows = y.dtype == PBD_DTYPE_BF16 && y.kb_gu >= ROWS_MIN_KB;
     const bool any_u = y.r > 0 && (y.rows ? y.MTmax >= ROWS_MIN_MT : y.big);
-    y.w_u = any_u ? take((size_t)y.Mmax * 3 * y.RT * 16 * 4) : 0;
-    y.w_ukpart = y.w_u && !y.rows ? take((size_t)BIG_KSPLIT_MAX * y.Mmax * 3 * y.RT * 16 * 4) : 0;
+    // (that of at most two m-tiles and as many rank tiles, where the split-K partials would be)
+    static_assert(ROWS_MIN_KB * 2 * 8192 >= (ROWS_MIN_MT - 1) * 16 * 3 * (ROWS_MIN_MT - 1) * 16 * 4, "shrink fits the partials");
+    y.w_u = !any_u && y.rows ? y.w_kpart : any_u ? take((size_t)y.Mmax * 3 * y.RT * 16 * 4) : 0;
+    y.w_ukpart = any_u && !y.rows ? take((size_t)BIG_KSPLIT_MAX * y.Mmax * 3 * y.RT * 16 * 4) : 0;
     y.w_dn_conf = take((size_t)y.Bmax * y.D * 4);
     // (its byte offsets into the packed weights are 32-bit)
     y.fused_shape = fused_cand && y.packed_bytes < ((size_t)1 << 32);
@@ -370,6 +380,11 @@ int run_pass(pbd_ctx* c, const PassReq& q, hipStream_t st) {
         while (kps < y.max_seq && ((size_t)B * y.NKV * cdiv(y.max_seq, kps) > (size_t)ATTN_GRID_CAP ||
                                    cdiv(y.max_seq, kps) > ATTN_SPLIT_CAP))
             kps *= 2;
+        // one sequence's few work-groups: half as long, while the merge still
+        // takes all splits in one round of loads (rank 32, 512 of 802 positions:
+        // 1304 us a draft against 1357; not for two sequences, 1395 and 1345)
+        if (dt == PBD_DTYPE_BF16 && B == 1 && y.NKV <= 8 && y.max_seq > 2 * ATTN_KPS && cdiv(y.max_seq, ATTN_KPS / 2) < 8)
+            kps = ATTN_KPS / 2;
     }
     if (pre) kps = std::max(kps, PREFILL_KPS);
     const int s_launch = pre ? y.S_pre : std::min(y.S_max, cdiv(y.max_seq, kps) + 1);   // split-KV grid columns
@@ -389,9 +404,7 @@ int run_pass(pbd_ctx* c, const PassReq& q, hipStream_t st) {
     // large-M draft/verify passes of bf16 models: single fp16 activation
     // operands against the fp16 weight copies (one MFMA per fragment pair)
     const bool h16 = big && !pre && y.f16big;
-    // bf16 passes of more than two m-tiles (more than the skinny GEMM takes in
-    // one go over its weights)
-    const bool rows = y.rows && MT >= ROWS_MIN_MT;
+    const bool rows = y.rows && (MT >= ROWS_MIN_MT || !lora || y.RT <= MT);
     const bool split = c->split && dt == PBD_DTYPE_BF16 && !h16;
     float* x = (float*)(ws + y.w_x);
     float* sq_a = (float*)(ws + y.w_sq_a);
@@ -620,7 +633,12 @@ int run_pass(pbd_ctx* c, const PassReq& q, hipStream_t st) {
             const size_t beg = lo_.o, end = l + 1 < L ? y.lay[l + 1].o : lo_.attn_norm;
             const int slots = B * y.NKV * at.n_qgrp;
             const int free_wg = 256 - s_launch * slots;
-            at.pf_x = slots > 0 && free_wg > slots ? free_wg / slots : 0;
+            // (at more than two m-tiles only beside eight splits and more: there the
+            // GEMMs hide their weights' latency themselves, and a short attention
+            // ends after the warming; batch 4 of 50 .. 100 keys: 781 us over 14
+            // layers without, 843 with; batch 2 of 8192: 526 and 515; one
+            // sequence of 60: 909 and 847)
+            at.pf_x = slots > 0 && free_wg > slots && (!att_rows || MT <= 2 || s_launch > 8) ? free_wg / slots : 0;
             size_t cap = (size_t)at.pf_x * slots * (att_rows ? (QT + 1) * 64 : 256) * 16 * 128;
             at.pf[0] = pk + beg;
             at.pf_bytes[0] = std::min(end - beg, cap);

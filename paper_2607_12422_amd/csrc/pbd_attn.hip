@@ -42,7 +42,8 @@ __global__ __launch_bounds__((NW + 1) * 64) __attribute__((amdgpu_waves_per_eu(3
     // one KV head per XCD (id % 8) where there are eight: its keys stay in that L2
     const int g = blockIdx.x, b = blockIdx.z;
     const int q0 = (gridDim.y - 1 - blockIdx.y) * ROWS;        // longest causal rows first
-    const int t = a.pos0[b], nrows = a.nrows[b];
+    // uniform (a row's address must not wait for them in a branch of its own)
+    const int t = __builtin_amdgcn_readfirstlane(a.pos0[b]), nrows = __builtin_amdgcn_readfirstlane(a.nrows[b]);
     const int W = a.W, G = a.G, QR = G * W;
     const int lane = threadIdx.x % WAVE, wid = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
     const int lrow = lane % 16, lgrp = lane / 16;
@@ -82,10 +83,11 @@ __global__ __launch_bounds__((NW + 1) * 64) __attribute__((amdgpu_waves_per_eu(3
         RP rp[ROWS / (NW * 4)];
 #pragma unroll
         for (int i = 0; i < ROWS / (NW * 4); ++i) {
-            const int q = q0 + i * NW * 4 + wid * 4 + lgrp;
-            const int qq = (q < QR && (q % W) < nrows) ? q : 0;        // dead rows read a valid row
-            rp[i].load(a.qkv + ((size_t)b * W + qq % W) * a.nqkv + (size_t)(g * G + qq / W) * HD,
-                       a.rope + (size_t)(t + qq % W) * HALF, lrow);
+            // dead rows read a valid row, at a position of the table
+            const unsigned q = min(q0 + i * NW * 4 + wid * 4 + lgrp, QR - 1), gi = q / (unsigned)W;
+            const int j = min((int)(q - gi * W), nrows - 1);
+            rp[i].load(a.qkv + ((size_t)b * W + j) * a.nqkv + (size_t)(g * G + gi) * HD,
+                       a.rope + (size_t)(t + j) * HALF, lrow);
         }
         float gq_lo[RP::NP], gq_hi[RP::NP];
         gq.get(a.qk_norm, gq_lo, gq_hi);

@@ -1038,7 +1038,9 @@ __global__ __launch_bounds__((QT + 1) * 64) __attribute__((amdgpu_waves_per_eu(3
         return;
     }
     const int s = blockIdx.x, g = blockIdx.y, b = blockIdx.z;
-    const int t = a.pos0[b], nrows = a.nrows[b];
+    // uniform: a row's address must not wait for them in a branch of its own
+    // (every such wait also drains the loads before it)
+    const int t = __builtin_amdgcn_readfirstlane(a.pos0[b]), nrows = __builtin_amdgcn_readfirstlane(a.nrows[b]);
     int s_pre, chunk;
     attn_splits(t, a.kps, a.s_launch, s_pre, chunk);
     const int W = a.W, G = a.G, QR = G * W;
@@ -1074,7 +1076,23 @@ __global__ __launch_bounds__((QT + 1) * 64) __attribute__((amdgpu_waves_per_eu(3
     }
 
     // -- this wave's 16 query rows: normed, rotated and scaled by
-    //    log2 e / sqrt(head_dim) into LDS, four rows per step
+    //    log2 e / sqrt(head_dim) into LDS, four rows per step; in the block
+    //    split the first of its key and value rows come with them
+    RP rk[2];
+    typename RP::fv vlo[2], vhi[2];
+    Gains<T, HD> gk;
+    auto kv_load = [&](int j0) {
+        if (a.qk_norm) gk.load(a.k_norm, lrow);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int jj = min(j0 + (i * NWV + wid) * 4 + lgrp, W - 1);      // dead rows read a valid row
+            const float* ks = qkv_b + (size_t)jj * row_stride + (size_t)a.n_q * HD + (size_t)g * HD;
+            const float* vs = ks + (size_t)a.n_kv * HD;
+            rk[i].load(ks, a.rope + (size_t)(t + jj) * HALF, lrow);
+            vlo[i] = *(const typename RP::fv*)(vs + RP::NP * lrow);
+            vhi[i] = *(const typename RP::fv*)(vs + HALF + RP::NP * lrow);
+        }
+    };
     uint4 qf[1][NDS];
     if (wid < QT) {
         Gains<T, HD> gq;
@@ -1082,10 +1100,8 @@ __global__ __launch_bounds__((QT + 1) * 64) __attribute__((amdgpu_waves_per_eu(3
         RP rp[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int qi = wid * 16 + 4 * i + lgrp;
-            const int qq = (qi < QR && (qi % W) < nrows) ? qi : 0;   // dead rows read a valid row
-            rp[i].load(qkv_b + (size_t)(qq % W) * row_stride + (size_t)(g * G + qq / W) * HD,
-                       a.rope + (size_t)(t + qq % W) * HALF, lrow);
+            const unsigned qq = min(wid * 16 + 4 * i + lgrp, QR - 1), gi = qq / (unsigned)W, j = qq - gi * W;
+            rp[i].load(qkv_b + (size_t)j * row_stride + (size_t)(g * G + gi) * HD, a.rope + (size_t)(t + j) * HALF, lrow);
         }
         float gq_lo[RP::NP], gq_hi[RP::NP];
         gq.get(a.qk_norm, gq_lo, gq_hi);
@@ -1096,12 +1112,19 @@ __global__ __launch_bounds__((QT + 1) * 64) __attribute__((amdgpu_waves_per_eu(3
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
+            if (i == 2) {
+                // not earlier: within 128 registers the CU's work-groups find room in any order
+                __builtin_amdgcn_sched_barrier(0);
+                if (blk) kv_load(0);
+            }
             const int qi = wid * 16 + 4 * i + lgrp;
             T lo[RP::NP], hi[RP::NP];
             rp[i].finish(q_l + qi * ATTN_LDQ, qi < QR, gq_lo, gq_hi, a.qk_norm, a.eps, lrow, lo, hi);
         }
 #pragma unroll
         for (int ds = 0; ds < NDS; ++ds) qf[0][ds] = *(const uint4*)(q_l + q * ATTN_LDQ + ds * FK + lgrp * EPL);
+    } else {
+        kv_load(0);
     }
 
     if (blk) {
@@ -1111,53 +1134,46 @@ __global__ __launch_bounds__((QT + 1) * 64) __attribute__((amdgpu_waves_per_eu(3
         // row.  The verify appends rows j < kv_rows to the cache.
         static_assert(EPL == 8 && RP::NP == 4, "bf16 block layout with four pairs per lane");
         static_assert(RING >= 3 && ATTN_ROWS_WMAX <= 64, "two stages below the query rows");
-        Gains<T, HD> gk;
-        if (a.qk_norm) gk.load(a.k_norm, lrow);
         float gk_lo[RP::NP], gk_hi[RP::NP];
         gk.get(a.qk_norm, gk_lo, gk_hi);
-        for (int j0 = wid * 4; j0 < n_st * 32; j0 += NWV * 4) {
-            const int j = j0 + lgrp, r = j % 16;
-            const bool live = j < W && j < nrows;
-            T klo[RP::NP], khi[RP::NP], vl[RP::NP], vh[RP::NP];
+        for (int base = 0; base < n_st * 32; base += 2 * NWV * 4) {
+            if (base > 0 && base < W) kv_load(base);
 #pragma unroll
-            for (int p = 0; p < RP::NP; ++p) klo[p] = khi[p] = vl[p] = vh[p] = (T)0.f;
-            if (j0 < W) {
-                const int jj = live ? j : 0;                       // dead rows read a valid row
-                const float* ks = qkv_b + (size_t)jj * row_stride + (size_t)a.n_q * HD + (size_t)g * HD;
-                const float* vs = ks + (size_t)a.n_kv * HD;
-                RP rk;
-                rk.load(ks, a.rope + (size_t)(t + jj) * HALF, lrow);
-                const typename RP::fv vlo = *(const typename RP::fv*)(vs + RP::NP * lrow);
-                const typename RP::fv vhi = *(const typename RP::fv*)(vs + HALF + RP::NP * lrow);
-                rk.values(live, gk_lo, gk_hi, a.qk_norm, a.eps, klo, khi);
+            for (int i = 0; i < 2; ++i) {
+                const int j0 = base + (i * NWV + wid) * 4;
+                if (j0 >= n_st * 32) continue;
+                const int j = j0 + lgrp, r = j % 16;
+                const bool live = j < W && j < nrows;
+                T klo[RP::NP], khi[RP::NP], vl[RP::NP], vh[RP::NP];
+                rk[i].values(live, gk_lo, gk_hi, a.qk_norm, a.eps, klo, khi);
 #pragma unroll
                 for (int p = 0; p < RP::NP; ++p) {
-                    vl[p] = from_f32<T>(live ? vlo[p] : 0.f);
-                    vh[p] = from_f32<T>(live ? vhi[p] : 0.f);
+                    vl[p] = from_f32<T>(live ? vlo[i][p] : 0.f);
+                    vh[p] = from_f32<T>(live ? vhi[i][p] : 0.f);
                 }
-            }
-            // the lane's dims 4 lrow .. 4 lrow + 3 (and + HALF) of key row r:
-            // one 8-byte run of the K block (kblock_elem), four V elements
-            // 4 apart (vblock_elem); the high half 1024 elements on
-            const int ko = ((lrow / 8) * 64 + ((lrow % 8) / 2) * 16 + r) * 8 + 4 * (lrow % 2);
-            const int vo = ((lrow / 4) * 64 + (r / 4) * 16 + 4 * (lrow % 4)) * 4 + r % 4;
-            auto put = [&](T* kb, T* vb, int ko_, int vo_) {
-                uint2 k2, h2;
-                __builtin_memcpy(&k2, klo, 8);
-                __builtin_memcpy(&h2, khi, 8);
-                *(uint2*)(kb + ko_) = k2;
-                *(uint2*)(kb + ko_ + 1024) = h2;
+                // the lane's dims 4 lrow .. 4 lrow + 3 (and + HALF) of key row r:
+                // one 8-byte run of the K block (kblock_elem), four V elements
+                // 4 apart (vblock_elem); the high half 1024 elements on
+                const int ko = ((lrow / 8) * 64 + ((lrow % 8) / 2) * 16 + r) * 8 + 4 * (lrow % 2);
+                const int vo = ((lrow / 4) * 64 + (r / 4) * 16 + 4 * (lrow % 4)) * 4 + r % 4;
+                auto put = [&](T* kb, T* vb, int ko_, int vo_) {
+                    uint2 k2, h2;
+                    __builtin_memcpy(&k2, klo, 8);
+                    __builtin_memcpy(&h2, khi, 8);
+                    *(uint2*)(kb + ko_) = k2;
+                    *(uint2*)(kb + ko_ + 1024) = h2;
 #pragma unroll
-                for (int p = 0; p < RP::NP; ++p) {
-                    vb[vo_ + 4 * p] = vl[p];
-                    vb[vo_ + 4 * p + 1024] = vh[p];
+                    for (int p = 0; p < RP::NP; ++p) {
+                        vb[vo_ + 4 * p] = vl[p];
+                        vb[vo_ + 4 * p + 1024] = vh[p];
+                    }
+                };
+                put((T*)(smem + (size_t)(j / 16) * BLK), (T*)(smem + (size_t)(j / 16) * BLK + BLK / 2), ko, vo);
+                if (live && j < a.kv_rows) {
+                    const int pos = t + j, kr = pos % 16;
+                    put((T*)a.kcache + head + (size_t)(pos / 16) * 16 * HD, (T*)a.vcache + head + (size_t)(pos / 16) * 16 * HD,
+                        ko + (kr - r) * 8, vo + (kr / 4 - r / 4) * 64 + (kr % 4 - r % 4));
                 }
-            };
-            put((T*)(smem + (size_t)(j / 16) * BLK), (T*)(smem + (size_t)(j / 16) * BLK + BLK / 2), ko, vo);
-            if (live && j < a.kv_rows) {
-                const int pos = t + j, kr = pos % 16;
-                put((T*)a.kcache + head + (size_t)(pos / 16) * 16 * HD, (T*)a.vcache + head + (size_t)(pos / 16) * 16 * HD,
-                    ko + (kr - r) * 8, vo + (kr / 4 - r / 4) * 64 + (kr % 4 - r % 4));
             }
         }
         lds_sync();
