@@ -658,7 +658,7 @@ def main():
             gemm_bytes = args.steps * (byt["gemm_draft"] + byt["gemm_verify"])
             gemm_launch_bytes = gemm_bytes / max(g["launches"], 1)
             ach = gemm_launch_bytes / (g["avg_us"] * 1e-6) / 1e9 if g["launches"] else 0.0
-            result["roofline"] = {"bound": "hbm", "kernel": "k_fgemm (q/k/v, o, gate/up, down projections; both passes)",
+            result["roofline"] = {"bound": "hbm", "kernel": "k_gemm_ks (q/k/v, o, gate/up, down projections; both passes)",
                                   "achieved": round(ach, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                                   "frac": round(ach / HBM_PEAK_GBPS, 4),
                                   "traffic": counter_traffic("k_fgemm_traffic.txt", "pbd_kernels.hip"),
@@ -677,7 +677,7 @@ def main():
             if M >= MFMA16_PEAK_TFLOPS * 1e3 / HBM_PEAK_GBPS:
                 tflops = flops / (g["total_ms"] * 1e-3) / 1e12
                 result["gemm_roofline"] = {
-                    "bound": "mfma", "kernel": "k_gemm_big (projections and LoRA shrinks; both passes)",
+                    "bound": "mfma", "kernel": "k_gemm_ks / k_gemm_tile (projections and LoRA shrinks; both passes)",
                     "achieved": round(tflops, 1), "peak": MFMA16_PEAK_TFLOPS, "unit": "TFLOP/s",
                     "frac": round(tflops / MFMA16_PEAK_TFLOPS, 4), "traffic": None,
                     "flops_per_launch": round(flops / g["launches"]), "avg_launch_us": g["avg_us"]}
@@ -685,7 +685,7 @@ def main():
                 gbytes = args.steps * (byt["gemm_draft"] + byt["gemm_verify"])
                 ach = gbytes / (g["total_ms"] * 1e-3) / 1e9
                 result["gemm_roofline"] = {
-                    "bound": "hbm", "kernel": "k_gemm_big (projections and LoRA shrinks; both passes)",
+                    "bound": "hbm", "kernel": "k_gemm_ks / k_gemm_tile (projections and LoRA shrinks; both passes)",
                     "achieved": round(ach, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                     "frac": round(ach / HBM_PEAK_GBPS, 4), "traffic": None,
                     "bytes_per_launch": round(gbytes / g["launches"]), "avg_launch_us": g["avg_us"]}
@@ -699,7 +699,7 @@ def main():
                 traffic = (counter_traffic("k_attn_rows_traffic_qwen3-0.6b_b32_p8192.txt", "pbd_kernels.hip")
                            if w_.name == "qwen3-0.6b-b32-p8192-d32" else None)
                 result["attn_roofline"] = {
-                    "bound": "hbm", "kernel": "attention partials over the prefix K/V (k_attn_rows at 4-5 query tiles per KV head, else k_attn)",
+                    "bound": "hbm", "kernel": "attention partials over the prefix K/V (k_attn_rows)",
                     "achieved": round(ach, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                     "frac": round(ach / HBM_PEAK_GBPS, 4), "traffic": traffic,
                     "bytes_per_launch": round(kv_bytes / at_["launches"]), "avg_launch_us": at_["avg_us"],

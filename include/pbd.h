@@ -150,8 +150,7 @@ typedef struct pbd_weights {
  * layer's projection and LoRA A fragments, which that pass streams.  A bf16
  * model whose max_batch * (block + 1) is at least 128 (draft and verify
  * passes on the large-M GEMM) also gets those copies and an fp16 copy of the
- * embedding fragments (the tied LM head), read by those passes; its
- * workspace also holds the LoRA shrink's K slices (up to eight).
+ * embedding fragments (the tied LM head), read by those passes.
  */
 size_t pbd_packed_weight_bytes(const pbd_config* cfg);
 size_t pbd_kv_bytes(const pbd_config* cfg);

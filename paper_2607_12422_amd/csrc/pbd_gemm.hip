@@ -1,5 +1,6 @@
-// Projection GEMM of passes with more than two 16-row m-tiles (bf16 models):
-// K split over the waves of a work-group.
+// Projection GEMM of bf16 models: K split over the waves of a work-group.  (Few
+// rows with an adapter of high rank stay on the skinny GEMM; passes of many
+// rows take the LDS blocks of pbd_tile.hip where gemm_pick says so.)
 //
 //   Y[m][n] = r_m * ( sum_k W[n][k] X[m][k]  +  s * sum_j B[n][j] u[m][j] ),
 //   u[m][j] = sum_k A[j][k] X[m][k]                    (LoRA, adapter on)

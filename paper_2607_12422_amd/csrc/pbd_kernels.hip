@@ -1,6 +1,8 @@
 // HIP kernels of the PEFT-BD speculative step for gfx950.
 //
-// One pass (draft or verify, Sec. 3 steps 1-3) runs six kernels per layer:
+// One pass (draft or verify, Sec. 3 steps 1-3) runs six kernels per layer (bf16
+// models take the projections of pbd_gemm.hip in k_fgemm's place, k_attn_rows or
+// the prefill attention of pbd_attn.hip in k_attn's):
 //   k_fgemm<STORE>   q/k/v projection; RMSNorm folded in as a per-row scale of the
 //                    accumulator; LoRA shrink A x and expand B u inside the tile
 //                    (App. A.2) when the adapter is on

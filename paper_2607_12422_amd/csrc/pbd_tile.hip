@@ -1,10 +1,10 @@
 // Projection GEMM of passes with many rows (bf16 models; the same products and
-// epilogues as pbd_gemm.hip): blocks of 8 to 12 x 8 to 16 16 x 16 tiles over
+// epilogues as pbd_gemm.hip): blocks of 4 to 12 x 8 to 16 tiles of 16 x 16 over
 // the whole K, operands and weights shared through LDS.
 //
 // WM x WN computing waves own TM x TN tiles each; NL more waves copy the
-// fragments of the block's next two K steps (packed, 1 KiB each) straight into
-// a ring of RING stages in LDS, so that the computing waves issue nothing but
+// fragments of the block's next K steps (packed, 1 KiB each; KST steps a stage)
+// straight into a ring of RING stages in LDS, so that the computing waves issue nothing but
 // LDS reads and MFMAs.  One barrier per stage: the loaders wait for the stage's
 // fragments before it, and fill the slot it releases after it.  A fragment
 // comes to the CU once per block and to the registers once per wave row or

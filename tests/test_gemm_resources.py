@@ -1,5 +1,5 @@
-"""Compile-time checks of the K-split projection GEMM (CPU, needs hipcc): no
-instance keeps data in scratch memory, none needs more than the 256 registers
+"""Compile-time checks of the K-split and LDS-tiled projection GEMMs and the
+prefill attention (CPU, needs hipcc): no instance keeps data in scratch memory, none needs more than the 256 registers
 per lane that two waves a SIMD leave, and no vector instruction reads an MFMA
 result too early (see test_mfma_hazards)."""
 import os
@@ -12,7 +12,7 @@ import pytest
 from paper_2607_12422_amd import build as b
 from test_mfma_hazards import early_reads
 
-SOURCES = ("pbd_gemm.hip",)
+SOURCES = ("pbd_gemm.hip", "pbd_tile.hip", "pbd_attn.hip")
 
 
 @pytest.mark.slow
@@ -29,8 +29,8 @@ def test_gemm_kernels_use_no_scratch_and_wait_for_mfma(tmp_path):
         scratch = [int(x) for x in re.findall(r"ScratchSize \[bytes/lane\]: (\d+)", r.stdout)]
         vgprs = [int(x) for x in re.findall(r" VGPRs: (\d+)", r.stdout)]
         agprs = [int(x) for x in re.findall(r" AGPRs: (\d+)", r.stdout)]
-        assert len(scratch) > 10 and max(scratch) == 0, scratch
+        assert scratch and max(scratch) == 0, (src, scratch)
         assert max(v + a for v, a in zip(vgprs, agprs)) <= 256
         asm = out.read_text()
-        assert asm.count("v_mfma") > 100, src
+        assert asm.count("v_mfma") >= 32, src
         assert not early_reads(asm)[:10]
