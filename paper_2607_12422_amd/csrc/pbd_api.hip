@@ -52,6 +52,8 @@ hipError_t scratch_address(int dev, hipStream_t st, char** out) {
 
 constexpr int MAX_DIM = 16384;   // bound on hidden, ffn and n_q_heads*head_dim
 constexpr int LMHEAD_GRID = 512;  // work-groups of the persistent LM head (two per CU)
+constexpr int CHUNK_KEYS = 1024;  // prefill attention without a key split: at most this many keys, or at
+constexpr int CHUNK_GROUPS = 64;  // least this many work-groups
 constexpr int PREFILL_KPS = 1024; // keys per attention split in prefill chunks (many query groups)
 constexpr int ATTN_KPS = 256;     // keys per attention split of a step pass, doubled while the grid is too
 constexpr int ATTN_GRID_CAP = 1280; // large (batch x KV heads x splits above this, 5 per CU) or there are
@@ -393,7 +395,13 @@ int run_pass(pbd_ctx* c, const PassReq& q, hipStream_t st) {
     // when the split grid leaves CUs idle or a work item has at most three
     // query tiles (the one-tile work-group runs two waves per SIMD)
     const bool att_rows = c->qsplit <= 0 && attn_rows_fits(dt, y.HD, QT, pre ? 1 : 0, W);
-    const bool att_chunk = pre && attn_chunk_fits(dt, y.HD);
+    // prefill chunks of bf16 models: launch_attn_chunk, unless its work-groups of
+    // 64 query rows over all keys would be few and long (a 4096-token prompt over
+    // four layers: 17-row chunks 77.7 ms, with the keys split over k_attn's 62.4;
+    // 128-row 11.6 and 10.7; 256-row, 64 work-groups, 6.60 and 6.87; 800 tokens in
+    // 17-row chunks 11.82 and 11.86)
+    const bool att_chunk = pre && attn_chunk_fits(dt, y.HD) &&
+                           (q.chunk_pos + W <= CHUNK_KEYS || B * y.NKV * cdiv(y.G * W, 64) >= CHUNK_GROUPS);
     const bool qsplit = !att_rows && (pre || c->qsplit > 0 || (c->qsplit < 0 && (QT <= 3 || B * y.NKV * s_launch < 256)));
     const int QTw = qsplit ? 1 : QT;                // ... per attention work-group
     const float scale = y.r > 0 ? c->cfg.lora_alpha / (float)y.r : 0.f;
