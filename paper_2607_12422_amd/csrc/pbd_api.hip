@@ -106,7 +106,7 @@ struct Layout {
     size_t w_xc[2], w_sqc;                           // prefill: gathered last rows (LM-head operand, Σx² partials)
     bool rows;                                       // passes of >= ROWS_MIN_MT m-tiles use launch_gemm_rows
     bool big;                                        // passes of >= BIG_MIN_MT m-tiles can use the large-M GEMM
-    size_t w_u;                                      // its LoRA shrink u = A x, [M][sources * RT * 16] fp32
+    size_t w_u;                                      // LoRA shrink u = A x of many rows, [M][sources * RT * 16] fp32
     size_t w_ukpart;                                 // the shrink's split-K slices [BIG_KSPLIT_MAX][w_u]
     size_t w_dn_tok, w_dn_conf;                      // one denoising pass's candidates and confidences
     int ksplit;                                      // K slices of the residual GEMMs
@@ -241,6 +241,10 @@ void make_layout(const pbd_config* c, Layout& y) {
     y.w_attn_ml = take(nrow_part * 2 * 4);
     y.w_arg_val = take((size_t)y.tiles_e * y.Mmax * 4);
     y.w_arg_idx = take((size_t)y.tiles_e * y.Mmax * 4);
+    // LoRA shrink of the projections of many rows: no attention or argmax partial
+    // is alive while a projection runs (few heads and a tiny vocabulary: past their end)
+    y.w_u = y.w_attn_o;
+    if (y.r > 0) off = std::max(off, align_up(y.w_u + (size_t)y.Mmax * 3 * y.RT * 16 * 4, 256));
     y.w_tokens = take((size_t)y.Mmax * 4);
     y.w_pos0 = take((size_t)y.Bmax * 4);
     y.w_nrows = take((size_t)y.Bmax * 4);
@@ -255,13 +259,8 @@ void make_layout(const pbd_config* c, Layout& y) {
     y.w_xc[0] = take(y.kb_e * xfc); y.w_xc[1] = take(nlo * y.kb_e * xfc);
     y.w_sqc = take((size_t)std::max(y.tiles_d, 1) * y.Bmax * 4);
     y.big = y.Mmax >= BIG_MIN_MT * 16;
-    // LoRA shrink of the projections of many rows
     y.rows = y.dtype == PBD_DTYPE_BF16 && y.kb_gu >= ROWS_MIN_KB;
-    const bool any_u = y.r > 0 && (y.rows ? y.MTmax >= ROWS_MIN_MT : y.big);
-    // (that of at most two m-tiles and as many rank tiles, where the split-K partials would be)
-    static_assert(ROWS_MIN_KB * 2 * 8192 >= (ROWS_MIN_MT - 1) * 16 * 3 * (ROWS_MIN_MT - 1) * 16 * 4, "shrink fits the partials");
-    y.w_u = !any_u && y.rows ? y.w_kpart : any_u ? take((size_t)y.Mmax * 3 * y.RT * 16 * 4) : 0;
-    y.w_ukpart = any_u && !y.rows ? take((size_t)BIG_KSPLIT_MAX * y.Mmax * 3 * y.RT * 16 * 4) : 0;
+    y.w_ukpart = y.r > 0 && y.big && !y.rows ? take((size_t)BIG_KSPLIT_MAX * y.Mmax * 3 * y.RT * 16 * 4) : 0;
     y.w_dn_conf = take((size_t)y.Bmax * y.D * 4);
     // (its byte offsets into the packed weights are 32-bit)
     y.fused_shape = fused_cand && y.packed_bytes < ((size_t)1 << 32);
@@ -408,7 +407,7 @@ int run_pass(pbd_ctx* c, const PassReq& q, hipStream_t st) {
     const bool lora = q.adapter && y.r > 0;
     // passes of many rows (prefill chunks, large-batch steps): large-M
     // projections, with the residual / SwiGLU epilogues in the GEMM
-    const bool big = MT >= BIG_MIN_MT && y.big && (!lora || y.w_u != 0);
+    const bool big = MT >= BIG_MIN_MT && y.big;
     // large-M draft/verify passes of bf16 models: single fp16 activation
     // operands against the fp16 weight copies (one MFMA per fragment pair)
     const bool h16 = big && !pre && y.f16big;

@@ -97,3 +97,19 @@ def test_calls_reject_null_context(lib):
 def test_missing_library_fails_loudly(tmp_path):
     with pytest.raises(RuntimeError, match="not built"):
         b.load_library(str(tmp_path / "libpbd.so"))
+
+
+def test_shrink_needs_no_workspace_of_its_own(lib):
+    """pbd_verify_block_noalloc refuses a context whose workspace exceeds the
+    static scratch: the LoRA shrink of many-row passes lies over regions that
+    are idle meanwhile, so a rank adds nothing.  Two sequences of 25 rows at
+    rank 48 and 848 positions are within 17 KiB of the limit."""
+    base = synth.QWEN3_0_6B.with_(block=24)
+    limit = 32 << 20
+    for rank in (24, 48, 64):
+        with_rank = b.make_config(base.with_(lora_rank=rank, lora_alpha=2.0 * rank), 2, 848)
+        assert limit - (17 << 10) < lib.pbd_workspace_bytes(ctypes.byref(with_rank)) <= limit
+    for mb, block in ((1, 16), (4, 16), (7, 16), (40, 8)):
+        sizes = {lib.pbd_workspace_bytes(ctypes.byref(b.make_config(
+            base.with_(block=block, lora_rank=r, lora_alpha=128.0), mb, 512))) for r in (24, 48, 64)}
+        assert len(sizes) == 1
