@@ -381,19 +381,23 @@ int run_pass(pbd_ctx* c, const PassReq& q, hipStream_t st) {
         while (kps < y.max_seq && ((size_t)B * y.NKV * cdiv(y.max_seq, kps) > (size_t)ATTN_GRID_CAP ||
                                    cdiv(y.max_seq, kps) > ATTN_SPLIT_CAP))
             kps *= 2;
-        // one sequence's few work-groups: half as long, while the merge still
-        // takes all splits in one round of loads (rank 32, 512 of 802 positions:
-        // 1304 us a draft against 1357; not for two sequences, 1395 and 1345)
-        if (dt == PBD_DTYPE_BF16 && B == 1 && y.NKV <= 8 && y.max_seq > 2 * ATTN_KPS && cdiv(y.max_seq, ATTN_KPS / 2) < 8)
-            kps = ATTN_KPS / 2;
     }
     if (pre) kps = std::max(kps, PREFILL_KPS);
     const int s_launch = pre ? y.S_pre : std::min(y.S_max, cdiv(y.max_seq, kps) + 1);   // split-KV grid columns
-    // draft and verify passes of bf16 models take launch_attn_rows; other shapes
+    // draft and verify passes of bf16 models take launch_attn_rows, except those of
+    // one sequence, whose grid leaves the chip idle: there k_attn's four waves
+    // share a split's keys, a chain a quarter as long (verify over four
+    // Qwen3-0.6B layers, 17 rows, 300 / 780 / 2000 / 4000 keys: 158 / 160 / 163 /
+    // 176 us against 160 / 168 / 174 / 194; two sequences: 176 / 177 / 192 / 222
+    // against 172 / 179 / 191 / 217).  Four or five query tiles read the keys as
+    // often: only where there are many (33 rows: 182 / 186 / 190 / 200 us against
+    // 177 / 182 / 198 / 223).  k_attn takes
     // one work-group per 16 query rows: always for prefill chunks; by default
     // when the split grid leaves CUs idle or a work item has at most three
     // query tiles (the one-tile work-group runs two waves per SIMD)
-    const bool att_rows = c->qsplit <= 0 && attn_rows_fits(dt, y.HD, QT, pre ? 1 : 0, W);
+    const bool one_seq = B == 1 && (QT <= 3 || s_launch > 8);
+    const bool rows_fit = attn_rows_fits(dt, y.HD, QT, pre ? 1 : 0, W);
+    const bool att_rows = rows_fit && (c->qsplit == 0 || (c->qsplit < 0 && !one_seq));
     // prefill chunks of bf16 models: launch_attn_chunk, unless its work-groups of
     // 64 query rows over all keys would be few and long (a 4096-token prompt over
     // four layers: 17-row chunks 77.7 ms, with the keys split over k_attn's 62.4;
@@ -401,7 +405,7 @@ int run_pass(pbd_ctx* c, const PassReq& q, hipStream_t st) {
     // 17-row chunks 11.82 and 11.86)
     const bool att_chunk = pre && attn_chunk_fits(dt, y.HD) &&
                            (q.chunk_pos + W <= CHUNK_KEYS || B * y.NKV * cdiv(y.G * W, 64) >= CHUNK_GROUPS);
-    const bool qsplit = !att_rows && (pre || c->qsplit > 0 || (c->qsplit < 0 && (QT <= 3 || B * y.NKV * s_launch < 256)));
+    const bool qsplit = !att_rows && (pre || rows_fit || c->qsplit > 0 || (c->qsplit < 0 && (QT <= 3 || B * y.NKV * s_launch < 256)));
     const int QTw = qsplit ? 1 : QT;                // ... per attention work-group
     const float scale = y.r > 0 ? c->cfg.lora_alpha / (float)y.r : 0.f;
     const bool lora = q.adapter && y.r > 0;

@@ -53,6 +53,33 @@ def test_tiles_and_splits_match_oracle(block, lengths, kps):
     g.close()
 
 
+@pytest.mark.parametrize("batch,block,max_seq,keys,mode", [
+    (1, 16, 802, 256, 1),           # one sequence, up to three tiles: one work-group per tile
+    (1, 7, 300, 256, 1),
+    (1, 32, 802, 256, 0),           # ... five tiles, few splits: one work-group per KV head
+    (1, 32, 2100, 256, 1),          # ... and nine of them
+    (2, 16, 802, 256, 0),           # more sequences: one work-group per KV head
+    (5, 16, 8300, 512, 0),          # 5 x 8 x 33 work items of 256 keys are too many
+])
+def test_automatic_layout_is_the_documented_one(batch, block, max_seq, keys, mode):
+    """The automatic keys per split and layout give bitwise what the values
+    that pbd.h names for them give."""
+    cfg = SHAPE.with_(n_layers=1, block=block, lora_rank=32, lora_alpha=64.0)
+    w = synth.make_weights(cfg, 93)
+    g = GpuRun(cfg, w, max_batch=batch, max_seq=max_seq)
+    g.prefill(synth.make_prompts(cfg, [260 - 7 * b for b in range(batch)], 10))
+    _, automatic = g.draft()
+    g.eng.pbd_set_attn_keys_per_split(keys)
+    g.eng.pbd_set_attn_query_split(mode)
+    _, named = g.draft()
+    assert g.status() == 0
+    assert bool((automatic == named).all())
+    g.eng.pbd_set_attn_query_split(1 - mode)
+    _, other = g.draft()
+    assert not bool((other == named).all())
+    g.close()
+
+
 @pytest.mark.parametrize("chunk,lengths", [
     (1, [3, 5, 1]),                 # one row per pass
     (31, [40, 1, 62]),              # a row block over both query heads
