@@ -67,6 +67,13 @@ constexpr int ATTN_SPLIT_CAP = 16;  // more splits than this (their partials cos
 // against 1438; two 16-row blocks at rank 16: 734 against 816, at rank 32: 716
 // against 757).
 constexpr int ROWS_MIN_KB = 8;
+// What the attention of a bf16 pass warms for the next kernels at most: what the
+// memory delivers while a short attention lasts.  More holds the next kernel up
+// (draft of one sequence of 300, four layers of hidden 2560, 5 x 16 query rows,
+// rank 16: 590 us with 32 MiB, 600 with 64, 661 without a bound, 606 when the
+// bound was 75 MB; Qwen3-0.6B layers, verify: 165 us with 40 MiB, 176 with 64),
+// less leaves it idle (hidden 2048, rank 64: 545 us with 40 MiB, 564 with 32).
+constexpr size_t WARM_BYTES = (size_t)40 << 20;
 constexpr int ROWS_MIN_MT = 3;   // m-tiles from which every rank does
 constexpr int BIG_MIN_MT = 8;    // passes of >= 128 rows (prefill chunks, batches of 8+) use the large-M projection
 constexpr size_t MAX_LDS = 160 * 1024;   // LDS one gfx950 work-group may allocate
@@ -651,6 +658,7 @@ int run_pass(pbd_ctx* c, const PassReq& q, hipStream_t st) {
             // sequence of 60: 909 and 847)
             at.pf_x = slots > 0 && free_wg > slots && (!att_rows || MT <= 2 || s_launch > 8) ? free_wg / slots : 0;
             size_t cap = (size_t)at.pf_x * slots * (att_rows ? (QT + 1) * 64 : 256) * 16 * 128;
+            if (dt == PBD_DTYPE_BF16) cap = std::min(cap, WARM_BYTES);
             at.pf[0] = pk + beg;
             at.pf_bytes[0] = std::min(end - beg, cap);
             cap -= at.pf_bytes[0];
