@@ -381,39 +381,58 @@ float tile_cost(const TileInst& c, int n_tiles, int kb, int MT, bool resid) {
 
 struct Pick {
     hipError_t (*launch)(BigGemmArgs, hipStream_t);
-    int bn;
+    int bm, bn;
     float us;
+    bool lds;          // pbd_tile.hip's
+    int nw;            // waves of a K-split block
 };
 
 // The LM head's K-split blocks (four waves, four tiles) and the LDS blocks
 // made for it leave one argmax partial per row and block.
 Pick gemm_pick(int pair, int st, int n_tiles, int kb, int MT, bool argmax, bool resid) {
-    Pick best{nullptr, 0, 0.f};
-    auto take = [&](hipError_t (*launch)(BigGemmArgs, hipStream_t), int bn, float us) {
-        if (!best.launch || us < best.us) best = Pick{launch, bn, us};
+    Pick best{};
+    auto take = [&](const Pick& p) {
+        if (!best.launch || p.us < best.us) best = p;
     };
     for (const Inst& c : INST)
         if (c.pair == pair && c.st == st && (!argmax || (c.nw == 4 && c.nb == 4)))
-            take(c.launch, c.nb, ks_cost(c, n_tiles, kb, MT));
+            take(Pick{c.launch, c.mb, c.nb, ks_cost(c, n_tiles, kb, MT), false, c.nw});
     int n = 0;
     const TileInst* ti = tile_insts(&n);
     for (int i = 0; i < n && st == 0 && kb % 2 == 0; ++i)
         if (ti[i].pair == pair && ti[i].arg == (argmax ? 1 : 0))
-            take(ti[i].launch, ti[i].bn, tile_cost(ti[i], n_tiles, kb, MT, resid));
+            take(Pick{ti[i].launch, ti[i].bm, ti[i].bn, tile_cost(ti[i], n_tiles, kb, MT, resid), true, 0});
     return best;
 }
 
 }  // namespace
 
-int gemm_rows_shrink_tiles(const BigGemmArgs& a) {
-    // LoRA shrink inside the projection (its A tiles beside the weights in
-    // every block) or as a launch of its own (4.5 us): whichever is less
-    const int st = (a.lora_mode == LORA_ROW_HALF ? 2 : 1) * a.lrt;
-    if (a.lrt <= 0 || !(st == 1 || st == 2 || st == 4)) return 0;
-    const int pair = a.op_f16 ? 0 : 1;
-    const float in = gemm_pick(pair, st, a.n_tiles, a.kb, a.MT, false, a.rx != nullptr).us;
-    const float ext = gemm_pick(pair, 0, a.n_tiles, a.kb, a.MT, false, a.rx != nullptr).us + 4.5f;
+int gemm_shrink_tiles(int pair, int nsrc, bool half, int lrt, int n_tiles, int kb, int MT, bool resid) {
+    // LoRA shrink inside the projection (its A tiles beside the weights in every
+    // block) or as a launch of its own, whose few blocks walk the whole K, and
+    // 0.5 us for u's way through memory: whichever is less.  (4.5 us for any
+    // launch took four layers of hidden 2560, one sequence, rank 16, from 530 us
+    // a draft to 593: down's K of 9728 makes it 16.8 us.  Over 1 .. 32 sequences
+    // of 8, 17 and 33 rows, ranks 8 .. 64, four layer shapes, no draft is more
+    // than 2.4 % off the best of 0, 0.5, 1 and 1.5 us; with each of the others
+    // one is 7 to 8 %.)
+    const int st = half ? 2 * lrt : lrt;
+    if (lrt <= 0 || !(st == 1 || st == 2 || st == 4)) return 0;
+    const float in = gemm_pick(pair, st, n_tiles, kb, MT, false, resid).us;
+    const float ext = gemm_pick(pair, 0, n_tiles, kb, MT, false, resid).us +
+                      gemm_pick(pair, 0, nsrc * lrt, kb, MT, false, false).us + 0.5f;
     return in <= ext ? st : 0;
+}
+
+int gemm_rows_shrink_tiles(const BigGemmArgs& a) {
+    const int nsrc = a.lora_mode == LORA_BY_TILE ? 3 : a.lora_mode == LORA_ROW_HALF ? 2 : 1;
+    return gemm_shrink_tiles(a.op_f16 ? 0 : 1, nsrc, a.lora_mode == LORA_ROW_HALF, a.lrt, a.n_tiles, a.kb, a.MT, a.rx != nullptr);
+}
+
+int gemm_choice(int pair, int st, int n_tiles, int kb, int MT, bool argmax, bool resid, int* block) {
+    const Pick c = gemm_pick(pair, st, n_tiles, kb, MT, argmax, resid);
+    block[0] = c.lds ? 1 : 0; block[1] = c.bm; block[2] = c.bn; block[3] = c.nw;
+    return c.launch ? 1 : 0;
 }
 
 int gemm_rows_parts(const BigGemmArgs& a) {

@@ -333,13 +333,19 @@ struct KSumArgs {
 };
 hipError_t launch_ksum(const KSumArgs& a, hipStream_t st);
 hipError_t launch_gemm_big(int dtype, const BigGemmArgs& a, hipStream_t st);   // split iff a.xlo
-// Passes of more than two m-tiles of bf16 models (pbd_gemm.hip).  With the
-// adapter (a.lrt > 0): gemm_rows_shrink_tiles > 0 says that the launch runs the
-// shrink itself, on a.la; else a.u holds it.  The argmax epilogue leaves
+// Projections of bf16 models (pbd_gemm.hip; run_pass keeps few rows with more
+// rank tiles than m-tiles on launch_fgemm).  With the adapter (a.lrt > 0):
+// gemm_rows_shrink_tiles > 0 says that the launch runs the shrink itself, on
+// a.la; else a.u holds it.  The argmax epilogue leaves
 // gemm_rows_parts partials per row.
 hipError_t launch_gemm_rows(const BigGemmArgs& a, hipStream_t st);
 int gemm_rows_shrink_tiles(const BigGemmArgs& a);
 int gemm_rows_parts(const BigGemmArgs& a);
+// The rules behind them, for tests: shrink tiles of a projection with nsrc
+// sources of lrt tiles (half: gate/up), and the block that a launch takes,
+// block = {LDS block or K split, m-tiles, n-tiles, waves of the K split}
+int gemm_shrink_tiles(int pair, int nsrc, bool half, int lrt, int n_tiles, int kb, int MT, bool resid);
+int gemm_choice(int pair, int st, int n_tiles, int kb, int MT, bool argmax, bool resid, int* block);
 hipError_t launch_remask(const RemaskArgs& a, int batch, hipStream_t st);
 hipError_t launch_pack(int dtype, const PackArgs& a, hipStream_t st);
 hipError_t launch_pack_expand(int dtype, const PackExpandArgs& a, hipStream_t st);
