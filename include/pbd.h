@@ -335,8 +335,10 @@ int pbd_sync_status(pbd_ctx* ctx, pbd_stream_t stream, int32_t* status);
  * Attention split tuning: prefix keys per split-KV work item of the step
  * passes (a positive multiple of 16), or 0 (default) for automatic: 256,
  * doubled while batch * n_kv_heads * ceil(max_seq / keys) exceeds 1280 work
- * items or ceil(max_seq / keys) exceeds 16 splits.  Prefill chunks use at
- * least 1024.  Other values: PBD_ERR_INVALID_ARG.
+ * items or ceil(max_seq / keys) exceeds 16 splits.  Prefill chunks use the
+ * value too, at least 1024; automatic, those of bf16 models with head_dim 128
+ * split no keys where the chunk ends within 1024 positions or the chunk's
+ * query rows fill 64 work-groups.  Other values: PBD_ERR_INVALID_ARG.
  */
 int pbd_set_attn_keys_per_split(pbd_ctx* ctx, int32_t keys);
 

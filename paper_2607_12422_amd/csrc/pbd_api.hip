@@ -405,12 +405,13 @@ int run_pass(pbd_ctx* c, const PassReq& q, hipStream_t st) {
     const bool one_seq = B == 1 && (QT <= 3 || s_launch > 8);
     const bool rows_fit = attn_rows_fits(dt, y.HD, QT, pre ? 1 : 0, W);
     const bool att_rows = rows_fit && (c->qsplit == 0 || (c->qsplit < 0 && !one_seq));
-    // prefill chunks of bf16 models: launch_attn_chunk, unless its work-groups of
+    // prefill chunks of bf16 models: launch_attn_chunk, unless the caller set the
+    // keys per split (k_attn's at least 1024, as pbd.h says) or its work-groups of
     // 64 query rows over all keys would be few and long (a 4096-token prompt over
     // four layers: 17-row chunks 77.7 ms, with the keys split over k_attn's 62.4;
     // 128-row 11.6 and 10.7; 256-row, 64 work-groups, 6.60 and 6.87; 800 tokens in
     // 17-row chunks 11.82 and 11.86)
-    const bool att_chunk = pre && attn_chunk_fits(dt, y.HD) &&
+    const bool att_chunk = pre && c->kps == 0 && attn_chunk_fits(dt, y.HD) &&
                            (q.chunk_pos + W <= CHUNK_KEYS || B * y.NKV * cdiv(y.G * W, 64) >= CHUNK_GROUPS);
     const bool qsplit = !att_rows && (pre || rows_fit || c->qsplit > 0 || (c->qsplit < 0 && (QT <= 3 || B * y.NKV * s_launch < 256)));
     const int QTw = qsplit ? 1 : QT;                // ... per attention work-group

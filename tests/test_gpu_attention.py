@@ -11,6 +11,7 @@ import pytest
 import synth
 from gpu_harness import GpuRun, decisive
 from oracle import model as om
+from paper_2607_12422_amd import binding
 
 pytestmark = pytest.mark.gpu
 
@@ -102,4 +103,28 @@ def test_prefill_chunks_match_oracle(chunk, lengths):
         st.anchor = int(first[b])
         _, ref, _, _ = om.verify(m, st, np.full(cfg.block, 9))
         assert np.abs(vlg[b].cpu().numpy() - ref).max() <= 2e-2
+    g.close()
+
+
+@pytest.mark.parametrize("keys,splits", [(0, False), (2048, True)])
+def test_keys_per_split_reach_the_prefill(keys, splits):
+    """Keys per split set by the caller split a prefill chunk's attention too
+    (there are partials to merge); automatic, a short prompt's is not split."""
+    cfg = SHAPE
+    w = synth.make_weights(cfg, 94)
+    prompts = synth.make_prompts(cfg, [600], 11)
+    g = GpuRun(cfg, w, max_batch=1, max_seq=700, prefill_chunk=600)
+    g.eng.pbd_set_attn_keys_per_split(keys)
+    g.eng.pbd_profile_enable(True)
+    first = g.prefill(prompts)
+    _, merges = g.eng.pbd_profile_read(binding.KCLASSES.index("combine"))
+    g.eng.pbd_profile_enable(False)
+    assert (merges == cfg.n_layers) if splits else (merges == 0)
+    v, vlg = g.verify(g.i32(np.full((1, cfg.block), 9)))
+    assert g.status() == 0
+    m = om.OracleModel(w)
+    st = om.prefill(m, prompts[0])
+    st.anchor = int(first[0])
+    _, ref, _, _ = om.verify(m, st, np.full(cfg.block, 9))
+    assert np.abs(vlg[0].cpu().numpy() - ref).max() <= 2e-2
     g.close()
