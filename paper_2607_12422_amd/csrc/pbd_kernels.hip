@@ -1836,7 +1836,11 @@ hipError_t launch_attn(int dtype, int head_dim, int qt, const AttnArgs& a, int b
     dim3 grid(a.s_launch + a.pf_x, a.n_kv, batch * a.n_qgrp);
     const size_t smem = attn_smem_bytes(dtype, head_dim, qt);
     if (dtype == PBD_DTYPE_BF16) {
-        if (head_dim == 128) return launch_attn_hd<bf16, 128>(a, qt, grid, smem, st);
+        if (head_dim == 128) {            // more query rows per work-group: launch_attn_rows
+            if (qt != 1) return hipErrorInvalidValue;
+            PBD_LAUNCH((k_attn<bf16, 128, 1>), grid, dim3(256), smem, st, a);
+            return hipGetLastError();
+        }
         if (head_dim == 64) return launch_attn_hd<bf16, 64>(a, qt, grid, smem, st);
     } else {
         if (head_dim == 128) return launch_attn_hd<float, 128>(a, qt, grid, smem, st);

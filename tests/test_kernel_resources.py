@@ -4,9 +4,9 @@ A register array indexed with a run-time value, or a register budget that
 overflows, puts per-lane data in scratch memory, which turns every access into
 a global memory round trip.  The kernels of the Qwen3-shape passes (the persistent
 layer stack; bf16 with split operands; projection GEMMs at every LoRA rank up to 64; attention with
-head_dim 128 and up to three 16-row query tiles, and the prefix splits of
-four or five) and every projection GEMM of
-the fp32 model must use no scratch at all.
+head_dim 128, in one work-group per query tile or per KV head with one to five
+of them) and every projection GEMM of the fp32 model must use no scratch at all.
+No other instance of the attention with head_dim 128 is built.
 """
 import os
 import re
@@ -21,8 +21,8 @@ HOT = [
     # projection GEMMs (bf16 value + residual operands; fp32), LoRA rank <= 64
     r"_ZN3pbd7k_fgemmIDF16bLi\d+ELi\d+ELb1ELi[0-4]EEEvNS_9FGemmArgsE",
     r"_ZN3pbd7k_fgemmIfLi\d+ELi\d+ELb0ELi[0-4]EEEvNS_9FGemmArgsE",
-    r"_ZN3pbd6k_attnIDF16bLi128ELi[123]EEEvNS_8AttnArgsE",            # attention, G*W <= 48 query rows
-    r"_ZN3pbd11k_attn_rowsILi[45]EEEvNS_8AttnArgsE",                  # prefix splits, 49..80 query rows
+    r"_ZN3pbd6k_attnIDF16bLi128ELi1EEEvNS_8AttnArgsE",                # attention, one work-group per 16 query rows
+    *(rf"_ZN3pbd11k_attn_rowsILi{qt}EEEvNS_8AttnArgsE" for qt in range(1, 6)),   # ... per KV head, 1..80 query rows
     r"_ZN3pbd8k_lmheadIDF16bLb1ELb[01]EEEvNS_9FGemmArgsE",            # LM head (with / without confidence)
     r"_ZN3pbd9k_combineIDF16bLi\d+EEEvNS_11CombineArgsE",
     r"_ZN3pbd10k_assembleIDF16bEEvNS_12AssembleArgsE",
@@ -66,3 +66,5 @@ def test_hot_kernels_use_no_scratch(tmp_path):
             seen += 1
             assert usage[n] == 0, f"{n} uses {usage[n]} bytes of scratch per lane"
     assert seen >= 15
+    built = {n for n in usage if re.search(r"6k_attnIDF16bLi128E", n)}
+    assert built == {"_ZN3pbd6k_attnIDF16bLi128ELi1EEEvNS_8AttnArgsE"}
