@@ -333,18 +333,20 @@ struct Inst {
     hipError_t (*launch)(BigGemmArgs, hipStream_t);
 };
 #define KS(P, MB, NB, NW, ST) {P, MB, NB, NW, ST, launch_ks<P, MB, NB, NW, ST>}
-#define KS_LORA(P, ST)                                                                                             \
-    KS(P, 1, 1, 8, ST), KS(P, 2, 1, 8, ST), KS(P, 3, 1, 8, ST), KS(P, 2, 2, 8, ST), KS(P, 3, 2, 8, ST), KS(P, 2, 4, 8, ST)
+#define KS_PAIR(ST) KS(1, 1, 1, 8, ST), KS(1, 2, 1, 8, ST), KS(1, 2, 2, 8, ST), KS(1, 3, 2, 8, ST), KS(1, 2, 4, 8, ST)
+#define KS_F16(ST) \
+    KS(0, 1, 1, 8, ST), KS(0, 2, 1, 8, ST), KS(0, 3, 1, 8, ST), KS(0, 2, 2, 8, ST), KS(0, 3, 2, 8, ST), KS(0, 2, 4, 8, ST)
 const Inst INST[] = {
-    KS(0, 1, 1, 8, 0), KS(0, 1, 2, 8, 0), KS(0, 2, 1, 8, 0), KS(0, 3, 1, 8, 0), KS(0, 5, 1, 8, 0), KS(0, 2, 2, 8, 0),
+    KS(0, 1, 1, 8, 0), KS(0, 1, 2, 8, 0), KS(0, 2, 1, 8, 0), KS(0, 3, 1, 8, 0), KS(0, 2, 2, 8, 0),
     KS(0, 3, 2, 8, 0), KS(0, 4, 2, 8, 0), KS(0, 5, 2, 8, 0), KS(0, 4, 4, 8, 0), KS(0, 2, 4, 4, 0), KS(0, 4, 4, 4, 0),
     KS(0, 5, 4, 4, 0),
     KS(1, 1, 1, 8, 0), KS(1, 1, 2, 8, 0), KS(1, 2, 1, 8, 0), KS(1, 2, 2, 8, 0), KS(1, 3, 2, 8, 0), KS(1, 4, 2, 8, 0),
     KS(1, 2, 4, 8, 0), KS(1, 4, 4, 8, 0), KS(1, 4, 4, 4, 0), KS(1, 5, 4, 4, 0),
-    KS_LORA(0, 1), KS_LORA(0, 2), KS_LORA(0, 4), KS_LORA(1, 1), KS_LORA(1, 2), KS_LORA(1, 4),
+    KS_F16(1), KS_F16(2), KS_F16(4), KS_PAIR(1), KS_PAIR(2), KS_PAIR(4),
 };
 #undef KS
-#undef KS_LORA
+#undef KS_PAIR
+#undef KS_F16
 
 // Times (us) behind the choice of an instance, fitted to all of them at 34 to
 // 4096 rows of the Qwen3-0.6B projections.

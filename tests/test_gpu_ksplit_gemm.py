@@ -1,5 +1,6 @@
-"""GPU parity of the K-split projection GEMM (bf16 passes of more than 32 rows)
-at the edges of its blocks: one row past an m-tile, a last block with missing
+"""GPU parity of the K-split and LDS-tiled projection GEMMs (bf16 passes; here of
+more than 32 rows, test_gpu_gemm_instances.py has the blocks that these do not
+reach) at the edges of their blocks: one row past an m-tile, a last block with missing
 m-tiles, a vocabulary whose last block has missing tiles; LoRA ranks whose
 shrink runs inside the projection (one, two and four A tiles) and as a launch
 of its own (three; four with two sources); the softmax partials of its LM head
