@@ -1,5 +1,5 @@
-"""GPU parity of the attention of draft and verify passes (bf16, head_dim 128)
-at the edges of its work split: one to five 16-row query tiles per KV head with
+"""GPU parity of the attention of draft and verify passes and of prefill chunks
+(bf16, head_dim 128) at the edges of its work split: one to five 16-row query tiles per KV head with
 a full or a nearly empty last tile, prefixes around the 16-key blocks, the
 32-key stages and the depth of their ring, splits of one block, of an odd
 number of blocks and automatic ones, a block of two stages.  Logits against the

@@ -8,8 +8,8 @@ that hold at any size are checked on the whole batch instead:
 
 * a sequence's logits do not depend on the rest of the batch, to within
   1e-2 (half the oracle tolerance): the batch's row count selects the GEMM
-  (a batch of 32 runs its prefill and step projections as the large-M GEMM,
-  one sequence alone the skinny one), whose different accumulation orders can
+  (a batch of 32 runs its prefill and step projections in LDS-tiled blocks,
+  one sequence alone in K-split ones), whose different accumulation orders can
   round the bf16 K/V cache differently; a row of another sequence leaking in
   would show as an O(1) error;
 * with the adapter off and a causal mask override, the draft pass over
@@ -177,9 +177,10 @@ def test_config5_full_batch_properties_and_sampled_sequence():
     del olg, mlg
 
     # sequence independence: sequence 0 alone gives the same logits up to the
-    # rounding differences of its kernels.  Alone (33 rows) it runs the skinny
-    # projection GEMM and the automatic keys per split of a batch of one; in
-    # the batch (1056 rows) the large-M GEMM and longer splits.  The two sum
+    # rounding differences of its kernels.  Alone (33 rows) it runs the K-split
+    # projection GEMM on value + residual operands and the automatic keys per
+    # split of a batch of one; in the batch (1056 rows) the LDS-tiled GEMM on
+    # fp16 operands and longer splits.  The two sum
     # in different orders and round the attention weights to bf16 over
     # different splits: 2.6e-3 (draft) / 2.2e-3 (verify) measured, bound 5e-3.
     g1 = GpuRun(cfg, w, max_batch=1, max_seq=max_seq, dev_weights=g.dw)

@@ -1,9 +1,11 @@
-"""GPU parity of the skinny projection GEMM at LoRA ranks 32, 48 and 64.
+"""GPU parity of passes of few rows at LoRA ranks 32, 48 and 64.
 
-Batches of one to three sequences keep every pass below the large-M path, so
-the adapter runs inside the weight-streaming GEMM with two to four 16-row
-shrink tiles per source matrix (App. A.2 fixes r = 16; the larger ranks are
-those of the batch-8 and batch-32 workloads).  Each sequence's draft and
+Batches of one to three sequences keep every pass on value + residual operands:
+the adapter has two to four 16-row shrink tiles per source matrix (App. A.2
+fixes r = 16; the larger ranks are those of the batch-8 and batch-32
+workloads).  The fp32 model runs them inside the skinny weight-streaming GEMM,
+the bf16 model only where there are more of them than tiles of rows (at most
+two), else in the K-split GEMM.  Each sequence's draft and
 verify logits are compared with the oracle: max-abs 1e-4 for the fp32 model,
 2e-2 for bf16; token ids equal at decisive rows.  The bf16 model has the
 Qwen3-0.6B layer shape with two layers and a 4096-token vocabulary, so that
@@ -77,3 +79,10 @@ def test_fp32_high_rank_adapter_matches_oracle(rank, batch):
 def test_bf16_high_rank_adapter_matches_oracle(rank, batch):
     cfg = synth.QWEN3_0_6B.with_(n_layers=2, vocab=4096, lora_rank=rank, lora_alpha=2.0 * rank)
     _run(cfg, 2e-2, batch, 4200 + rank + batch)
+
+
+@pytest.mark.parametrize("block,rank,batch", [(8, 32, 1), (15, 32, 1), (7, 64, 2), (8, 48, 1), (31, 64, 1), (31, 48, 1)])
+def test_bf16_more_rank_tiles_than_row_tiles_matches_oracle(block, rank, batch):
+    """One or two m-tiles: the adapter on the skinny GEMM."""
+    cfg = synth.QWEN3_0_6B.with_(n_layers=2, vocab=4096, block=block, lora_rank=rank, lora_alpha=2.0 * rank)
+    _run(cfg, 2e-2, batch, 4300 + rank + block)
