@@ -55,22 +55,34 @@ def algorithmic_bytes(cfg, batch, prefixes):
     )
 
 
-def counter_traffic(name, source):
+# the source files that the kernels with a counter summary are built from
+FUSED_SOURCES = ("pbd_fused.hip", "pbd_fused.h", "pbd_device.h", "pbd_kernels.h")
+ATTN_SOURCES = ("pbd_kernels.hip", "pbd_attn.h", "pbd_device.h", "pbd_kernels.h", "pbd_launch.h")
+GEMM_SOURCES = ("pbd_gemm.hip", "pbd_tile.hip", "pbd_epi.h", "pbd_device.h", "pbd_kernels.h", "pbd_launch.h")
+
+
+def source_sha256(sources):
+    import hashlib
+    h = hashlib.sha256()
+    for s in sources:
+        with open(os.path.join(ROOT, "paper_2607_12422_amd", "csrc", s), "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()
+
+
+def counter_traffic(name, sources):
     """HBM bytes per launch of a kernel from a committed rocprofv3 counter
     summary (FETCH_SIZE and WRITE_SIZE passes, scaled by a plain copy's
     readings).  None when the summary is missing or was taken on another
-    version of the kernel's source file."""
-    import hashlib
+    version of any file that the kernel is built from."""
     path = os.path.join(ROOT, "profiles", name)
-    src = os.path.join(ROOT, "paper_2607_12422_amd", "csrc", source)
     try:
         kv = {}
         for line in open(path):
             if ":" in line and not line.startswith("#"):
                 k, v = line.split(":", 1)
                 kv[k.strip()] = v.strip()
-        digest = hashlib.sha256(open(src, "rb").read()).hexdigest()
-        if kv.get("kernel_source_sha256") != digest:
+        if kv.get("kernel_source_sha256") != source_sha256(sources):
             return None
         return float(kv["traffic_bytes_per_launch"])
     except (OSError, KeyError, ValueError):
@@ -651,20 +663,23 @@ def main():
             result["roofline"] = {
                 "bound": "hbm", "kernel": "k_fused (persistent layer stack of the draft and the verify pass)",
                 "achieved": round(ach, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": round(ach / HBM_PEAK_GBPS, 4),
-                "traffic": counter_traffic("k_fused_traffic.txt", "pbd_fused.hip"),
+                "traffic": counter_traffic("k_fused_traffic.txt", FUSED_SOURCES),
                 "bytes_per_launch": round(launch_bytes), "avg_launch_us": fz["avg_us"]}
         else:
             g = prof["gemm"]
             gemm_bytes = args.steps * (byt["gemm_draft"] + byt["gemm_verify"])
             gemm_launch_bytes = gemm_bytes / max(g["launches"], 1)
             ach = gemm_launch_bytes / (g["avg_us"] * 1e-6) / 1e9 if g["launches"] else 0.0
-            result["roofline"] = {"bound": "hbm", "kernel": "k_gemm_ks (q/k/v, o, gate/up, down projections; both passes)",
+            # (the summary is of the batch-1 Qwen3-0.6B passes with one kernel per operator)
+            qwen1 = w_.name == "qwen3-0.6b-b1-p512"
+            kern = "k_gemm_ks" if cfg.dtype == "bf16" else "k_fgemm"
+            result["roofline"] = {"bound": "hbm", "kernel": kern + " (q/k/v, o, gate/up, down projections; both passes)",
                                   "achieved": round(ach, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                                   "frac": round(ach / HBM_PEAK_GBPS, 4),
-                                  "traffic": counter_traffic("k_fgemm_traffic.txt", "pbd_kernels.hip"),
+                                  "traffic": counter_traffic("k_gemm_ks_traffic.txt", GEMM_SOURCES) if qwen1 else None,
                                   "bytes_per_launch": round(gemm_launch_bytes), "avg_launch_us": g["avg_us"]}
         if not fz["launches"] and B * cfg.width >= 128 and prof["gemm"]["launches"]:
-            # passes of >= 128 rows: the projections run on the large-M GEMM,
+            # passes of >= 128 rows: the projections run on fp16 operands,
             # bound by the matrix cores (2 flops per weight and row, the
             # adapter's shrink and expand in the draft), and the attention
             # streams the prefix K/V from HBM
@@ -696,7 +711,7 @@ def main():
                 kv_bytes = args.steps * 2 * cfg.n_layers * sum(lengths) * 2 * cfg.n_kv_heads * cfg.head_dim * es
                 ach = kv_bytes / (at_["total_ms"] * 1e-3) / 1e9
                 # counter traffic: taken for the batch-32 workload's k_attn_rows
-                traffic = (counter_traffic("k_attn_rows_traffic_qwen3-0.6b_b32_p8192.txt", "pbd_kernels.hip")
+                traffic = (counter_traffic("k_attn_rows_traffic_qwen3-0.6b_b32_p8192.txt", ATTN_SOURCES)
                            if w_.name == "qwen3-0.6b-b32-p8192-d32" else None)
                 result["attn_roofline"] = {
                     "bound": "hbm", "kernel": "attention partials over the prefix K/V (k_attn_rows)",
@@ -724,8 +739,8 @@ def main():
             eng.pbd_profile_enable(False)
             if n:
                 gb = 10 * (byt["gemm_draft"] + byt["gemm_verify"]) / n
-                po["k_fgemm_avg_launch_us"] = round(1e3 * ms / n, 3)
-                po["k_fgemm_frac"] = round(gb / (ms / n * 1e-3) / 1e9 / HBM_PEAK_GBPS, 4)
+                po["gemm_avg_launch_us"] = round(1e3 * ms / n, 3)
+                po["gemm_frac"] = round(gb / (ms / n * 1e-3) / 1e9 / HBM_PEAK_GBPS, 4)
             eng.pbd_set_pass_mode(0 if args.pass_mode < 0 else args.pass_mode)
             result["per_operator_mode"] = po
 

@@ -149,7 +149,7 @@ typedef struct pbd_weights {
  * pbd_set_pass_mode), the packed weights also hold an fp16 copy of every
  * layer's projection and LoRA A fragments, which that pass streams.  A bf16
  * model whose max_batch * (block + 1) is at least 128 (draft and verify
- * passes on the large-M GEMM) also gets those copies and an fp16 copy of the
+ * passes of 128 rows or more run on fp16 operands) also gets those copies and an fp16 copy of the
  * embedding fragments (the tied LM head), read by those passes.
  */
 size_t pbd_packed_weight_bytes(const pbd_config* cfg);

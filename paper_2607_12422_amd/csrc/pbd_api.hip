@@ -75,7 +75,8 @@ constexpr int ROWS_MIN_KB = 8;
 // less leaves it idle (hidden 2048, rank 64: 545 us with 40 MiB, 564 with 32).
 constexpr size_t WARM_BYTES = (size_t)40 << 20;
 constexpr int ROWS_MIN_MT = 3;   // m-tiles from which every rank does
-constexpr int BIG_MIN_MT = 8;    // passes of >= 128 rows (prefill chunks, batches of 8+) use the large-M projection
+constexpr int BIG_MIN_MT = 8;    // large-M passes, >= 128 rows (batches of 8+): fp16 operands in bf16 models' draft
+                                 // and verify; fp32 and hidden < 256 take launch_gemm_big (prefill chunks too)
 constexpr size_t MAX_LDS = 160 * 1024;   // LDS one gfx950 work-group may allocate
 constexpr unsigned PBD_DEFAULT_WAIT = 1u << 18;   // polls per wait of the persistent pass (~0.25 s)
 
@@ -111,8 +112,8 @@ struct Layout {
     size_t w_kpart, w_kcnt;                          // split-K partial tiles and arrival counters
     size_t w_arg_mx, w_arg_sum;                      // LM-head softmax partials (draft confidence)
     size_t w_xc[2], w_sqc;                           // prefill: gathered last rows (LM-head operand, Σx² partials)
-    bool rows;                                       // passes of >= ROWS_MIN_MT m-tiles use launch_gemm_rows
-    bool big;                                        // passes of >= BIG_MIN_MT m-tiles can use the large-M GEMM
+    bool rows;                                       // launch_gemm_rows takes the projections (few rows: run_pass)
+    bool big;                                        // passes of >= BIG_MIN_MT m-tiles can be large-M passes
     size_t w_u;                                      // LoRA shrink u = A x of many rows, [M][sources * RT * 16] fp32
     size_t w_ukpart;                                 // the shrink's split-K slices [BIG_KSPLIT_MAX][w_u]
     size_t w_dn_tok, w_dn_conf;                      // one denoising pass's candidates and confidences
@@ -417,8 +418,8 @@ int run_pass(pbd_ctx* c, const PassReq& q, hipStream_t st) {
     const int QTw = qsplit ? 1 : QT;                // ... per attention work-group
     const float scale = y.r > 0 ? c->cfg.lora_alpha / (float)y.r : 0.f;
     const bool lora = q.adapter && y.r > 0;
-    // passes of many rows (prefill chunks, large-batch steps): large-M
-    // projections, with the residual / SwiGLU epilogues in the GEMM
+    // passes of many rows (prefill chunks, large-batch steps): unless `rows`,
+    // launch_gemm_big with the residual / SwiGLU epilogues in the GEMM
     const bool big = MT >= BIG_MIN_MT && y.big;
     // large-M draft/verify passes of bf16 models: single fp16 activation
     // operands against the fp16 weight copies (one MFMA per fragment pair)

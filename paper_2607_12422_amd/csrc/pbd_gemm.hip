@@ -1,5 +1,5 @@
-// Projection GEMM of bf16 models: K split over the waves of a work-group.  (Few
-// rows with an adapter of high rank stay on the skinny GEMM; passes of many
+// Projection GEMM of bf16 models: K split over the waves of a work-group.  (At
+// most two m-tiles with more rank tiles stay on the skinny GEMM; passes of many
 // rows take the LDS blocks of pbd_tile.hip where gemm_pick says so.)
 //
 //   Y[m][n] = r_m * ( sum_k W[n][k] X[m][k]  +  s * sum_j B[n][j] u[m][j] ),
@@ -349,11 +349,14 @@ const Inst INST[] = {
 #undef KS_F16
 
 // Times (us) behind the choice of an instance, fitted to all of them at 34 to
-// 4096 rows of the Qwen3-0.6B projections.
+// 4096 rows of the Qwen3-0.6B projections on 256 CUs.  They rank instances; what
+// all of a launch's candidates pay alike (the logits' stores of an LM head: 327
+// us estimated for 1056 rows, 414 measured) is left out.
 //
-// K-split blocks: a CU takes in 70 KiB of fragments a microsecond (the path
-// from the L2 bounds the loop, not the MFMAs), 62 over rounds of two
-// work-groups of four waves; one of those alone has its start and end to
+// K-split blocks: a CU takes in 70 KiB of fragments a microsecond in its loop
+// (fitted; over whole kernels the counters show 27 .. 36, 35 .. 40 requests in
+// flight per CU at 330 cycles, the MFMAs 11 .. 38 % busy and few L2 stalls, and so
+// name no single limit), 62 over rounds of two work-groups of four waves; one of those alone has its start and end to
 // itself.  Eight waves fill a CU, so a second round starts after the first
 // one's epilogue.
 float ks_cost(const Inst& c, int n_tiles, int kb, int MT) {
@@ -364,8 +367,8 @@ float ks_cost(const Inst& c, int n_tiles, int kb, int MT) {
     return blocks <= 256 ? 7.5f + kib / (c.pair ? 55.f : 80.f) : 4.f + rounds * kib / 62.f;
 }
 
-// LDS blocks: the same path (66 KiB a microsecond, 58 with operands in pairs,
-// whose twice as many products cover less of it), and an epilogue that grows
+// LDS blocks: the same loads (66 KiB a microsecond, 58 with operands in pairs,
+// whose twice as many products cover less of them), and an epilogue that grows
 // with the tiles of a wave and waits for the residual where there is one; one
 // work-group a CU.  At 1056 fp16 rows gate/up take 21.9 us in 8 x 16 tiles
 // (K-split: 28.6), q/k/v 16.8 in 10 x 8 (23.0), the LM head 414 in 12 x 12 or

@@ -303,16 +303,17 @@ hipError_t launch_assemble(int dtype, const AssembleArgs& a, int batch, hipStrea
 hipError_t launch_fgemm(int dtype, const FGemmArgs& a, int epi, hipStream_t st);   // split iff a.xlo
 int fgemm_mgroup(int epi, int MT, int lrt);   // lrt: LoRA rank tiles of the launch (0: adapter off)
 int fgemm_threads(int epi);         // work-group size of the GEMM with epilogue epi
-// The attention partials of a draft or verify pass with four or five 16-row
-// query tiles per KV head (bf16, head_dim 128, W <= 48): every split of
-// k_attn's schedule, one wave per query tile, keys staged through LDS
-// (false: this shape is not covered; use k_attn alone)
+// The attention partials of a draft or verify pass with one to five 16-row
+// query tiles per KV head (bf16, head_dim 128, W <= 64): every split of
+// k_attn's schedule, one wave per query tile, keys through an LDS ring
+// (false: this shape is not covered; use k_attn)
 bool attn_rows_fits(int dtype, int head_dim, int qt, int chunk, int W);
 hipError_t launch_attn_rows(const AttnArgs& a, int qt, int batch, hipStream_t st);
 // Prefill chunks (bf16, head_dim 128): every key of a 64-query-row block in one
 // work-group, O operand written directly (no partials, no merge)
 bool attn_chunk_fits(int dtype, int head_dim);
 hipError_t launch_attn_chunk(const AttnArgs& a, int batch, hipStream_t st);
+// (bf16 with head_dim 128: qt = 1 only)
 hipError_t launch_attn(int dtype, int head_dim, int qt, const AttnArgs& a, int batch, hipStream_t st);
 hipError_t launch_combine(int dtype, const CombineArgs& a, int M, hipStream_t st);
 hipError_t launch_argmax(const ArgmaxArgs& a, hipStream_t st);

@@ -1,8 +1,9 @@
 // HIP kernels of the PEFT-BD speculative step for gfx950.
 //
 // One pass (draft or verify, Sec. 3 steps 1-3) runs six kernels per layer (bf16
-// models take the projections of pbd_gemm.hip in k_fgemm's place, k_attn_rows or
-// the prefill attention of pbd_attn.hip in k_attn's):
+// models take the projections of pbd_gemm.hip in k_fgemm's place, but for few rows
+// of an adapter of high rank, and k_attn_rows or the prefill attention of
+// pbd_attn.hip in k_attn's, but for one sequence and chunks of few rows):
 //   k_fgemm<STORE>   q/k/v projection; RMSNorm folded in as a per-row scale of the
 //                    accumulator; LoRA shrink A x and expand B u inside the tile
 //                    (App. A.2) when the adapter is on
@@ -1007,7 +1008,8 @@ __global__ __launch_bounds__(256) void k_attn(AttnArgs a) {
 // Bound by memory at long prefixes: 248 us for 32 x 8192 keys at 66 query rows
 // (1.07 GB; 258 with keys staged through registers one block ahead; 238 with
 // the arithmetic left out, a large copy moves 4.8 TB/s), and by its chain of
-// launch, positions, queries and a few stages at short ones: 18.8 us for 8
+// launch, positions, queries and a few stages at short ones (a grid that leaves
+// the chip idle takes k_attn: run_pass): 18.8 us for 8
 // prefixes of 256 .. 2048 at 34 rows (26.5 with k_attn's one-tile
 // work-groups, which read the keys three times), 14.6 us for 16 of 256 .. 1024
 // at two rows (16.7).
@@ -1929,7 +1931,8 @@ hipError_t launch_gather_last(int dtype, const GatherArgs& a, int batch, hipStre
 }
 
 // ---------------------------------------------------------------------------
-// Large-M projection (prefill chunks, passes of many block rows).  The skinny
+// Large-M projection of fp32 models and of bf16 models with hidden < 256
+// (prefill chunks, passes of many block rows; the others: pbd_gemm.hip).  The skinny
 // GEMM above streams each weight tile once against every row; with hundreds of
 // rows it would re-read the operand per weight tile and wait a full load
 // latency per 64-row group.
