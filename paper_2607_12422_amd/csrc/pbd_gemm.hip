@@ -354,9 +354,9 @@ const Inst INST[] = {
 // us estimated for 1056 rows, 414 measured) is left out.
 //
 // K-split blocks: a CU takes in 70 KiB of fragments a microsecond in its loop
-// (fitted; over whole kernels the counters show 27 .. 36, 35 .. 40 requests in
-// flight per CU at 330 cycles, the MFMAs 11 .. 38 % busy and few L2 stalls, and so
-// name no single limit), 62 over rounds of two work-groups of four waves; one of those alone has its start and end to
+// (fitted; over whole kernels the counters show 17 .. 41, 27 .. 46 requests in
+// flight per CU at 310 .. 550 cycles, the MFMAs at most 38 % busy and hardly an L2
+// stall: they name no single limit), 62 over rounds of two work-groups of four waves; one of those alone has its start and end to
 // itself.  Eight waves fill a CU, so a second round starts after the first
 // one's epilogue.
 float ks_cost(const Inst& c, int n_tiles, int kb, int MT) {
