@@ -11,6 +11,15 @@ namespace pbd {
 // The running maximum is raised (and the output rescaled) only when a score
 // exceeds it by more than this (log2 units)
 constexpr float RESCALE_SLACK = 8.f;
+// ... in k_attn_rows.  A key at the maximum has the weight 1, which bf16 holds
+// exactly, and the largest weights carry the rounding error of the sum.  k_attn has
+// four maxima a split (and k_attn_chunk a block), one per wave; the one of
+// k_attn_rows has to follow its keys closer to be as near to float64: with 8 the
+// passes of up to three query tiles were 0.6 to 1.8 % further off than on k_attn,
+// with 1 they are 0 to 1.3 % nearer (error of logits against float64, two layers,
+// 2 to 16 sequences), in up to 0.4 % more time; with 0.5 0.1 to 1.7 %, in 0.3 to
+// 0.6 % more.
+constexpr float ROWS_SLACK = 1.f;
 
 // 32 keys in LDS: two 16-key blocks of the cache, each 4 KiB of K then 4 KiB of V
 constexpr int ATTN_STAGE = 16384;
@@ -87,12 +96,13 @@ static __device__ __forceinline__ void attn_loader(const char* kc, const char* v
 // online softmax per query column (exp2 domain) and O^T += V^T P^T with P^T
 // straight from the score accumulators.  The products over both key blocks
 // share one MFMA: its lane group g takes keys 4g .. 4g + 3 of either block, in
-// the values as in the weights.  masked: some (key, row) pairs are not seen;
+// the values as in the weights.  slack: how far a score may exceed the maximum
+// before it is raised.  masked: some (key, row) pairs are not seen;
 // ok(q, i): key i of the stage is seen by the lane's column of tile q.
 template <int TQ, typename OK>
 static __device__ __forceinline__ void attn_keys32(const unsigned char* st, int lane, const uint4 (&qf)[TQ][4],
                                                    f32x4 (&o)[TQ][8], float (&m)[TQ], float (&l)[TQ], bool first,
-                                                   bool masked, OK ok) {
+                                                   float slack, bool masked, OK ok) {
     const int lgrp = lane / 16;
     f32x4 sc[TQ][2];
 #pragma unroll
@@ -120,7 +130,7 @@ static __device__ __forceinline__ void attn_keys32(const unsigned char* st, int 
     bool over = first;
 #pragma unroll
     for (int q = 0; q < TQ; ++q) {
-        const float lim = m[q] + RESCALE_SLACK;
+        const float lim = m[q] + slack;
 #pragma unroll
         for (int c = 0; c < 2; ++c)
 #pragma unroll

@@ -131,8 +131,8 @@ __global__ __launch_bounds__((NW + 1) * 64) __attribute__((amdgpu_waves_per_eu(3
         lds_sync();
         const int k0 = it * KEYS + ks * 32;
         if (k0 > k_last || k0 >= k_end) continue;
-        attn_keys32<TQ>(smem + (size_t)((it & 1) * KS + ks) * ATTN_STAGE, lane, qf, o, m, l, false, k0 + 32 > k_full,
-                        [&](int q, int i) { return (k0 + i < k_end) & (k0 + i - t <= jq[q]); });
+        attn_keys32<TQ>(smem + (size_t)((it & 1) * KS + ks) * ATTN_STAGE, lane, qf, o, m, l, false, RESCALE_SLACK,
+                        k0 + 32 > k_full, [&](int q, int i) { return (k0 + i < k_end) & (k0 + i - t <= jq[q]); });
     }
 
     // merge of the key quarters: every wave leaves its sums, then takes two of

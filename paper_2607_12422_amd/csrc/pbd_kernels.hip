@@ -1192,7 +1192,7 @@ __global__ __launch_bounds__((QT + 1) * 64) __attribute__((amdgpu_waves_per_eu(3
     int slot = 0;
     for (int it = 0; it < n_st; ++it) {
         if (!blk) lds_sync();
-        attn_keys32<1>(smem + (size_t)slot * ATTN_STAGE, lane, qf, o_acc, m_run, l_run, it == 0,
+        attn_keys32<1>(smem + (size_t)slot * ATTN_STAGE, lane, qf, o_acc, m_run, l_run, it == 0, ROWS_SLACK,
                        blk || k_lo + it * 32 + 32 > k_hi, [&](int, int i) {
             // block key i is seen by block row jq iff i <= jq or jq >= full_from
             const int kk = it * 32 + i;

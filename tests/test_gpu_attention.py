@@ -81,6 +81,41 @@ def test_automatic_layout_is_the_documented_one(batch, block, max_seq, keys, mod
     g.close()
 
 
+@pytest.mark.parametrize("block,batch", [(0, 6), (7, 4), (16, 4), (31, 3)])
+def test_one_reference_maximum_is_no_less_precise(block, batch):
+    """k_attn_rows (layout 0) keeps one reference maximum per query row and
+    split, k_attn (layout 1) four: the weights that bf16 holds exactly are those
+    at a maximum.  On the same cache, the error of the verify's logits against
+    float64 (2-norm over all seeds) must not be larger than k_attn's by more
+    than twice the standard error of their ratio over the seeds."""
+    cfg = SHAPE.with_(n_layers=1, block=block)
+    err = np.zeros((2, 8))
+    for seed in range(err.shape[1]):
+        w = synth.make_weights(cfg, 300 + seed)
+        prompts = synth.make_prompts(cfg, [250 - 9 * b for b in range(batch)], 400 + seed)
+        g = GpuRun(cfg, w, max_batch=batch, max_seq=300)
+        first = g.prefill(prompts)
+        drafts = np.random.Generator(np.random.PCG64(seed)).integers(0, cfg.vocab - 1, size=(batch, max(block, 1)))
+        got = []
+        for mode in (0, 1):
+            g.eng.pbd_set_attn_query_split(mode)
+            _, lg = g.verify(g.i32(drafts[:, :block] if block else drafts))
+            got.append(lg.cpu().numpy().astype(np.float64))
+        assert g.status() == 0
+        g.close()
+        m = om.OracleModel(w)
+        for b in range(batch):
+            st = om.prefill(m, prompts[b])
+            st.anchor = int(first[b])
+            _, ref, _, _ = om.verify(m, st, drafts[b, :block])
+            for mode in (0, 1):
+                err[mode, seed] += ((got[mode][b] - ref) ** 2).sum()
+    err = np.sqrt(err)
+    ratio = np.log(err[0] / err[1])
+    print(f"block {block}: rows / one-tile {np.exp(ratio.mean()):.4f} +- {ratio.std(ddof=1) / len(ratio) ** 0.5:.4f}")
+    assert ratio.mean() <= 2 * ratio.std(ddof=1) / len(ratio) ** 0.5
+
+
 @pytest.mark.parametrize("chunk,lengths", [
     (1, [3, 5, 1]),                 # one row per pass
     (31, [40, 1, 62]),              # a row block over both query heads
