@@ -220,3 +220,28 @@ def test_wide_query_tiles_unanchored_matches_oracle():
     assert e <= 2e-2
     assert g.status() == 0
     g.close()
+
+
+@pytest.mark.parametrize("batch,block,rank", [
+    (2, 16, 16),        # 34 and 32 rows: the verify's two m-tiles on value + residual operands
+    (5, 16, 48),        # 85 rows, shrink of three tiles as a launch
+    (8, 15, 16),        # 128 and 120 rows: fp16 operands, half an m-tile missing in the verify
+    (24, 32, 64),       # 792 and 768 rows: LDS-tiled blocks
+])
+def test_bf16_batches_unanchored_match_oracle(batch, block, rank):
+    """The anchor row without the adapter, causal and with its K/V appended,
+    among the drafts of several sequences: one Qwen3-0.6B layer."""
+    cfg = synth.QWEN3_0_6B.with_(n_layers=1, vocab=4096, block=block, lora_rank=rank, lora_alpha=2.0 * rank)
+    w = synth.make_weights(cfg, 7600)
+    prompts = synth.make_prompts(cfg, [5 + (17 * b) % 90 for b in range(batch)], 7601)
+    g = GpuRun(cfg, w, max_batch=batch, max_seq=200)
+    first = g.prefill(prompts)
+    d, v, dlg = g.draft_unanchored()
+    v, vlg = g.verify_unanchored(d, v)
+    assert g.status() == 0
+    m = om.OracleModel(w)
+    for b in sorted({0, batch // 2, batch - 1}):
+        st = om.prefill(m, prompts[b])
+        st.anchor = int(first[b])
+        _round(g, m, st, b, d, v, dlg, vlg, 2e-2, what=f"sequence {b}")
+    g.close()
